@@ -337,20 +337,23 @@ cs_status cs_autotune(cs_ctx ctx, int32_t nrhs, int32_t *wgs, int64_t *grid, dou
 cs_status cs_set_graphs(cs_ctx ctx, int32_t on);
 cs_status cs_get_graphs(cs_ctx ctx, int32_t *on, double *eager_ms, double *graph_ms);
 
-/* Single-workgroup tail V-cycle (Alg. 1 on the small levels).  Levels below a
- * few thousand rows cost a kernel launch per sweep, transfer and direct solve
- * while moving almost no data; from the first level (the finest included) at
- * which every level has at most max_rows rows, the V-cycle from there down is
- * one launch of one workgroup of 512-1024 threads that runs the same per-row
+/* Tail V-cycle (Alg. 1 on the small levels).  Levels below a few thousand rows
+ * cost a kernel launch per sweep, transfer and direct solve while moving almost
+ * no data; from the first level (the finest included) at which every level has
+ * at most max_rows rows and the vectors of one system and right-hand side on
+ * all remaining levels fit the LDS of a CU (about 5,900 rows in FP64, 11,900 in
+ * FP32, the finest of them), the V-cycle from there down is one launch, a
+ * workgroup per system and right-hand side, that runs the same per-row
  * arithmetic with workgroup barriers in place of kernel boundaries, so results
  * are bit-identical to the per-level launches.  It applies to additive cascades
- * with fused aggregation transfers, one block size of 1, 2, 4 or 8 on the
- * covered levels, n_pre >= 1 and n_post >= 1; other hierarchies run the
- * per-level launches.  max_rows 0 switches it off (the default).  One
- * workgroup walks a level's 64-row slices one tile after another, so the tail
- * pays only on levels of a few tiles; cs_autotune times one V-cycle with the
- * tail off and starting at each level of at most 65536 rows and keeps the
- * fastest.  cs_vcycle_noalloc always runs the per-level launches.
+ * with one block size of 1, 2, 4 or 8 on the covered levels, n_pre >= 1 and
+ * n_post >= 1; other hierarchies run the per-level launches.  The systems are
+ * those of cs_set_systems where the transfers are aggregations and no row of a
+ * covered level couples two of them, else there is one.  max_rows 0 switches it
+ * off (the default).  One workgroup walks a system's rows 1024 at a time, so
+ * the tail pays only on levels of a few thousand rows; cs_autotune times one
+ * V-cycle with the tail off and starting at each level of at most 65536 rows
+ * and keeps the fastest.  cs_vcycle_noalloc always runs the per-level launches.
  * cs_get_tail returns max_rows, the first level the tail covers in the current
  * setup (-1: none) and, when cap > 0, up to cap of the last autotune's
  * candidates (cand_rows: the limit, 0 = off; cand_ms: one V-cycle in ms) with
@@ -379,7 +382,7 @@ typedef enum {
     CS_TRACE_REFINE = 5,        /* FP64 refinement residual and update */
     CS_TRACE_SWEEP_PROLONG = 6, /* first post-sweep with the interpolation fused in */
     CS_TRACE_SWEEP_SMALL = 7,   /* cascade sweeps that read A on small levels */
-    CS_TRACE_TAIL = 8,          /* the single-workgroup V-cycle over the coarse levels (cs_set_tail) */
+    CS_TRACE_TAIL = 8,          /* the one-launch V-cycle over the coarse levels (cs_set_tail) */
     CS_TRACE_NCLASS = 9
 } cs_trace_class;
 cs_status cs_trace(cs_ctx ctx, int32_t mask, int32_t period);

@@ -198,19 +198,22 @@ struct Level {
     unsigned char *w_ovl = nullptr;
 };
 
-// One level of the single-workgroup tail V-cycle (device copy of the
-// pointers and sizes the V-cycle uses on that level; values in the working
-// precision, cast by the kernel).
+// One level of the tail V-cycle (device copy of the pointers and sizes the
+// V-cycle uses on that level; values in the working precision, cast by the
+// kernel).  agg_k 0: transfers through P (p*) and P^T (t*) in sliced ELLPACK.
 struct TailLevel {
-    int64_t n, n_active, nslices, nc, nbl;   // rows, smoothed rows, their slices, coarse rows, Lambda entries per step
+    int64_t n_active, nbl;   // smoothed rows, Lambda entries per step
     const int64_t *sptr;
     const int32_t *slen, *scol;
     const void *sval, *lam, *lamT;
-    void *bb, *xb, *xt;
-    int depth, agg_k, nseg;
+    void *bb, *xb;
+    int depth, agg_k, nseg, max_len;   // max_len: entries of the longest smoothed row
     double r_scale;
     const int64_t *dseg, *dinv_off;
     const double *dinv;
+    const int64_t *pptr, *tptr;
+    const int32_t *plen, *pcol, *tlen, *tcol;
+    const void *pval, *tval;
 };
 
 struct Trace {
@@ -280,12 +283,16 @@ struct Ctx {
     // this FP64 vector (acc_done then true) instead of writing it
     double *acc_x64 = nullptr;
     bool acc_done = false;
-    // single-workgroup tail V-cycle over the coarse levels of at most tail_rows
+    // one-launch tail V-cycle over the coarse levels of at most tail_rows
     // rows (0: off); its level table, valid for (tail_gen, tail_prec, tail_nrhs)
     int64_t tail_rows = 0;
     int tail_from = -1;                 // first level the tail covers (-1: none)
     DBuf<TailLevel> tail_tab;
     std::vector<TailLevel> tail_host;
+    DBuf<int32_t> tail_sys;             // row offsets of the systems, [covered level][tail_nsys + 1]
+    std::vector<int32_t> tail_sys_host;
+    int tail_nsys = 1, tail_alt = 0;    // systems; LDS elements before the alternate buffer
+    int64_t tail_lds = 0;               // dynamic LDS of the tail kernel, bytes
     double tail_bytes = 0.0;            // algorithmic bytes of one tail launch (trace)
     std::vector<int64_t> tune_tail_rows;   // cs_autotune's candidates (0: off) and V-cycle ms
     std::vector<double> tune_tail_ms;
@@ -361,7 +368,17 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
               double *history, cs_status *st);
 void autotune(Ctx &c, int nrhs, double *ms_out);
 void tune_graphs(Ctx &c, int nrhs, double *eager_ms, double *graph_ms);
+
+// tail.hip: the small levels in one launch
 int tail_start(const Ctx &c);
+void tail_prepare(Ctx &c, int nrhs);
+// whether the tail runs the V-cycle from level l for nrhs right-hand sides
+inline bool tail_covers(const Ctx &c, int l, int nrhs) {
+    return l == c.tail_from && c.tail_gen == c.gen && c.tail_prec == c.precision && c.tail_nrhs == nrhs;
+}
+void tail_launch(Ctx &c, int nrhs, const double *b64 = nullptr, double *x64 = nullptr);
+
+// solve.hip
 int tune_tail(Ctx &c, int nrhs, int64_t *rows, double *ms, int cap);
 void stream_bandwidth(Ctx &c, int n_read, int n_write, int64_t bytes, int reps, double *gbps, double *us);
 void solve_gmres(Ctx &c, const double *b, double *x, int nrhs, double rtol, int maxit, int restart, bool flexible,

@@ -569,107 +569,6 @@ __global__ __launch_bounds__(WG) void k_direct_seg(int64_t n_active, int64_t n, 
     direct_row<T, R>(i, nseg, seg, inv_off, inv, b, x);
 }
 
-// ---------------------------------------------------------------------------
-// Single-workgroup tail V-cycle: the coarse levels of at most a few thousand
-// rows are latency-bound (a kernel of a few microseconds per sweep, transfer
-// and direct solve), so one workgroup of 512-1024 threads runs Alg. 1 on all of
-// them in one launch: the same per-row arithmetic as the per-level kernels
-// (sweep_tile, residual_restrict_tile, direct_row), a workgroup barrier where
-// the eager path has a kernel boundary, hence identical results.
-// ---------------------------------------------------------------------------
-// 1024 threads where a row's vector data fits in 8 bytes; 512 (twice the
-// registers per thread) for several right-hand sides
-template <typename T, int R>
-constexpr int tail_wg() { return R * sizeof(T) <= 8 ? 1024 : 512; }
-
-template <typename T, int NB, int R, int TW, bool ZERO, bool PROL>
-__device__ void tail_sweep(const TailLevel &L, const T *lam, const T *b, const T *xin, T *xout, const T *xc,
-                           T *red) {
-    constexpr int SPW = TW / 64;
-    const int64_t ntiles = (L.nslices + SPW - 1) / SPW;
-    for (int64_t tile = 0; tile < ntiles; ++tile)
-        sweep_tile<T, NB, R, ZERO, false, PROL, TW>(tile, L.n_active, L.nslices, nullptr, L.sptr, L.slen, L.scol,
-                                                        static_cast<const T *>(L.sval), lam, b, xin, xout, xc,
-                                                        L.agg_k, red);
-    __syncthreads();
-}
-
-// one application of the level's additive cascade (as apply_cascade); returns
-// the buffer that holds the result
-template <typename T, int NB, int R, int TW>
-__device__ T *tail_cascade(const TailLevel &L, bool reverse, bool zero_start, const T *b, T *x, T *alt,
-                           const T *xc, T *red) {
-    T *cur = x, *nxt = alt;
-    for (int s = 0; s < L.depth; ++s) {
-        const int ell = reverse ? L.depth - 1 - s : s;
-        const T *lam = static_cast<const T *>(reverse ? L.lamT : L.lam) + (int64_t)ell * L.nbl;
-        if (zero_start && s == 0) tail_sweep<T, NB, R, TW, true, false>(L, lam, b, cur, nxt, nullptr, red);
-        else if (s == 0 && xc) tail_sweep<T, NB, R, TW, false, true>(L, lam, b, cur, nxt, xc, red);
-        else tail_sweep<T, NB, R, TW, false, false>(L, lam, b, cur, nxt, nullptr, red);
-        T *t = cur;
-        cur = nxt;
-        nxt = t;
-    }
-    return cur;
-}
-
-template <typename T, int R, int TW>
-__device__ void tail_direct(const TailLevel &L, T *x) {
-    const int wv = threadIdx.x >> 6;
-    for (int64_t i = L.n_active + wv; i < L.n; i += TW / 64)
-        direct_row<T, R>(i, L.nseg, L.dseg, L.dinv_off, L.dinv, static_cast<const T *>(L.bb), x);
-    __syncthreads();
-}
-
-// Alg. 1 from tab[0] (its right-hand side already in tab[0].bb) to the last
-// entry, solved directly; the result in tab[0].xb.
-template <typename T, int NB, int R, int TW = tail_wg<T, R>()>
-__global__ __launch_bounds__(TW) void k_tail_vcycle(const TailLevel *__restrict__ tab, int nlev, int n_pre,
-                                                    int n_post, int rf) {
-    __shared__ T red[TW * R];
-    uint32_t in_alt = 0;   // bit l: level l's smoothed x sits in xt instead of xb
-    for (int l = 0; l + 1 < nlev; ++l) {
-        const TailLevel &L = tab[l];
-        T *x = static_cast<T *>(L.xb), *alt = static_cast<T *>(L.xt);
-        const T *b = static_cast<const T *>(L.bb);
-        for (int a = 0; a < n_pre; ++a) {
-            T *res = tail_cascade<T, NB, R, TW>(L, rf != 0, a == 0, b, x, alt, nullptr, red);
-            if (res != x) {
-                alt = x;
-                x = res;
-            }
-        }
-        if (x != static_cast<T *>(L.xb)) in_alt |= 1u << l;
-        constexpr int SPW = TW / 64;
-        const int64_t ntiles = (L.nslices + SPW - 1) / SPW;
-        for (int64_t tile = 0; tile < ntiles; ++tile)
-            residual_restrict_tile<T, R, NB, TW>(tile, L.n_active, L.nslices, L.sptr, L.slen, L.scol,
-                                                     static_cast<const T *>(L.sval), b, x, L.agg_k, L.nc,
-                                                     (T)L.r_scale, static_cast<T *>(tab[l + 1].bb), red);
-        __syncthreads();
-    }
-    tail_direct<T, R, TW>(tab[nlev - 1], static_cast<T *>(tab[nlev - 1].xb));
-    for (int l = nlev - 2; l >= 0; --l) {
-        const TailLevel &L = tab[l];
-        T *xb = static_cast<T *>(L.xb), *xt = static_cast<T *>(L.xt);
-        T *x = (in_alt >> l) & 1u ? xt : xb, *alt = x == xb ? xt : xb;
-        const T *b = static_cast<const T *>(L.bb);
-        const T *xc = static_cast<const T *>(tab[l + 1].xb);
-        for (int a = 0; a < n_post; ++a) {
-            T *res = tail_cascade<T, NB, R, TW>(L, false, false, b, x, alt, a == 0 ? xc : nullptr, red);
-            if (res != x) {
-                alt = x;
-                x = res;
-            }
-        }
-        if (x != xb) {
-            for (int64_t e = threadIdx.x; e < L.n_active * R; e += TW) xb[e] = x[e];
-            __syncthreads();
-        }
-        tail_direct<T, R, TW>(L, xb);
-    }
-}
-
 // Per-workgroup sums of W per-thread values into partial[blockIdx.x][W] (red:
 // (WG / 64) * W doubles): a wavefront butterfly, then the waves in order.
 template <int W>
@@ -1756,83 +1655,6 @@ void direct_solve(Ctx &c, const Level &L, const T *b, T *x) {
     trace_end(c, slot);
 }
 
-}  // namespace
-
-// The levels the tail kernel covers: the first level l (the finest included)
-// from which every level has at most c.tail_rows rows, every smoothed one is
-// additive (no overlapping blocks) with fused transfers and one common block
-// size of 1, 2, 4 or 8, and the cycle pre- and post-smooths (the first
-// post-smoothing sweep carries the interpolation); -1 when there is none.
-int tail_start(const Ctx &c) {
-    const int nl = (int)c.lv.size();
-    if (c.tail_rows <= 0 || nl < 2 || c.opt.mode != CS_ADDITIVE || !c.fuse_transfers || c.opt.n_pre < 1 ||
-        c.opt.n_post < 1)
-        return -1;
-    const int64_t nb = c.lv[nl - 2].nb;
-    if (nb != 1 && nb != 2 && nb != 4 && nb != 8) return -1;
-    int from = -1;
-    for (int l = nl - 1; l >= 0; --l) {
-        const Level &V = c.lv[l];
-        bool ok = V.n <= c.tail_rows && !V.ovl_m;
-        if (l + 1 < nl) ok = ok && V.agg_k > 0 && V.depth >= 1 && V.nb == nb && V.n_active > 0;
-        if (!ok || nl - l > 32) break;   // the kernel tracks the levels in a 32-bit mask
-        from = l;
-    }
-    return from >= 0 && from < nl - 1 ? from : -1;
-}
-
-namespace {
-
-template <typename T>
-void tail_table(Ctx &c, int nrhs) {
-    const int from = tail_start(c);
-    c.tail_from = from;
-    if (from < 0) return;
-    if (c.tail_gen == c.gen && c.tail_prec == c.precision && c.tail_nrhs == nrhs) return;
-    std::vector<TailLevel> tab;
-    const double es = sizeof(T), vr = (double)nrhs * es;
-    double bytes = 0.0;
-    for (size_t l = from; l < c.lv.size(); ++l) {
-        const Level &L = c.lv[l];
-        bytes += (double)L.dinv.n * 8.0 + 2.0 * (L.n - L.n_active) * vr;
-        if (l + 1 < c.lv.size()) {
-            const double A = L.act_nnz * (es + 4.0), lamb = (double)L.n_active * L.nb * es;
-            const double v = (double)L.n_active * vr, sweeps = (double)(c.opt.n_pre + c.opt.n_post) * L.depth;
-            bytes += (lamb + 2.0 * v) + (sweeps - 1.0) * (A + lamb + 3.0 * v);   // the first from zero
-            bytes += A + 2.0 * v + 2.0 * (double)L.nc * vr;   // residual + restriction, the interpolation read
-        }
-        TailLevel t{};
-        t.n = L.n;
-        t.n_active = L.n_active;
-        t.nslices = L.act_slices;
-        t.nc = L.nc;
-        t.nbl = L.B * L.nb * L.nb;
-        t.sptr = L.sell.slice_ptr.get();
-        t.slen = L.sell.slice_len.get();
-        t.scol = L.sell.col.get();
-        t.sval = sell_val<T>(L.sell);
-        t.lam = l + 1 < c.lv.size() ? lam_ptr<T>(L, false) : nullptr;
-        t.lamT = l + 1 < c.lv.size() ? lam_ptr<T>(L, true) : nullptr;
-        t.bb = L.w_bb;
-        t.xb = L.w_xb;
-        t.xt = L.w_xt;
-        t.depth = L.depth;
-        t.agg_k = L.agg_k;
-        t.r_scale = L.r_scale;
-        t.nseg = L.dseg.size() > 1 ? (int)L.dseg.size() - 1 : 0;
-        t.dseg = L.dseg_d.get();
-        t.dinv_off = L.dinv_off.get();
-        t.dinv = L.dinv.get();
-        tab.push_back(t);
-    }
-    c.tail_host = tab;
-    c.tail_bytes = bytes;
-    c.tail_tab.upload(c.tail_host.data(), c.tail_host.size(), c.stream);
-    c.tail_gen = c.gen;
-    c.tail_prec = c.precision;
-    c.tail_nrhs = nrhs;
-}
-
 // V-cycle (Alg. 1) from level l down: x_l = V(b_l) from the zero guess, with
 // b_l in bb and the result in xb.  Only the active rows are smoothed and
 // transferred; the direct segments of every level are solved exactly.
@@ -1857,19 +1679,8 @@ bool issue_first_sweep(Ctx &c) {
 
 template <typename T, int R>
 void vcycle_level(Ctx &c, int l) {
-    if (l == c.tail_from && c.tail_gen == c.gen && c.tail_prec == c.precision && c.tail_nrhs == R) {
-        const int nlev = (int)c.lv.size() - l;
-        hipEvent_t ev0 = nullptr, ev1 = nullptr;
-        const int slot = trace_begin_launch(c, CS_TRACE_TAIL, c.tail_bytes, &ev0, &ev1);
-        (void)slot;
-        dispatch_nb((int)c.lv[l].nb, [&](auto nbc) {
-            constexpr int NB = decltype(nbc)::value;
-            if constexpr (NB <= 8)
-                hipExtLaunchKernelGGL((k_tail_vcycle<T, NB, R>), dim3(1), dim3(tail_wg<T, R>()), 0, c.stream, ev0, ev1, 0,
-                                      (const TailLevel *)c.tail_tab.get(), nlev, c.opt.n_pre, c.opt.n_post,
-                                      c.opt.order == CS_RF ? 1 : 0);
-        });
-        CS_LAUNCH_CHECK();
+    if (tail_covers(c, l, R)) {
+        tail_launch(c, R);
         return;
     }
     Level &L = c.lv[l];
@@ -1975,16 +1786,11 @@ static void use_own_workspace(Ctx &c) {
     c.ws_scratch = false;
 }
 
-static void prepare_tail(Ctx &c, int nrhs) {
-    if (c.precision == CS_FP64) tail_table<double>(c, nrhs);
-    else tail_table<float>(c, nrhs);
-}
-
 void ensure_workspace(Ctx &c, int nrhs) {
     const int prec = c.precision;
     if (c.ws_nrhs == nrhs && c.ws_prec == prec) {
         if (c.ws_scratch) use_own_workspace(c);
-        prepare_tail(c, nrhs);
+        tail_prepare(c, nrhs);
         return;
     }
     const size_t es = prec == CS_FP64 ? sizeof(double) : sizeof(float);
@@ -2019,10 +1825,14 @@ void ensure_workspace(Ctx &c, int nrhs) {
     c.ws_nrhs = nrhs;
     c.gen++;
     c.ws_prec = prec;
-    prepare_tail(c, nrhs);
+    tail_prepare(c, nrhs);
 }
 
 static void vcycle_run(Ctx &c, const double *b, double *x, int nrhs) {
+    if (tail_covers(c, 0, nrhs)) {   // one launch: it reads b and writes x itself
+        tail_launch(c, nrhs, b, x);
+        return;
+    }
     Level &L0 = c.lv[0];
     const int64_t n = L0.n * nrhs;
     dispatch_prec(c.precision, [&](auto tp) {

@@ -1,0 +1,610 @@
+// Tail V-cycle (gfx950, wave64): the small levels of a V-cycle in one launch.
+#include <algorithm>
+#include <type_traits>
+
+#include <hip/hip_ext.h>
+
+#include "cs_internal.h"
+
+namespace cs {
+
+namespace {
+
+template <typename T, int N>
+__device__ __forceinline__ void vload(const T *p, T (&o)[N]) {   // N * sizeof(T) a power of two
+    if constexpr (N * sizeof(T) >= 16) {
+        const uint4 *q = reinterpret_cast<const uint4 *>(p);
+#pragma unroll
+        for (int k = 0; k < (int)(N * sizeof(T) / 16); ++k) {
+            const uint4 u = q[k];
+            __builtin_memcpy(&o[k * (16 / sizeof(T))], &u, 16);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < N; ++k) o[k] = p[k];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Tail V-cycle: the small levels are bound by latency (a kernel launch and
+// three dependent trips to the L2 per sweep, transfer and direct solve, for a
+// few KB of data), so Alg. 1 on all of them is one launch.  A workgroup of
+// 1024 threads runs the whole cycle for one right-hand side of one independent
+// system, with every level's x and b in LDS, a workgroup barrier where the
+// per-level path has a kernel boundary, and A, x and b of a thread's rows in
+// registers over all sweeps of a visit where a row has at most tail_ml entries
+// (longer rows stream from the L2).  The right-hand sides and the systems of a
+// batch do not see each other, so they go to different CUs.  Every row's
+// arithmetic is the per-level kernels' own, in the same order: identical
+// results.
+// What bounds it is one CU: about 0.5-1 us per sweep up to 1024 point rows and
+// 2 us at 4096 (a per-level launch takes 3.5-4 us), but 6 us for 2048 rows of
+// 8x8 blocks (110 KB of Lambda per sweep and system), so cs_autotune picks the
+// first level by timing.  One V(2,2) of the 64^2 FP64 problem: 142 us with a
+// launch per step, 93 us in the form with all vectors in the L2 and one
+// workgroup for all right-hand sides and systems, 51 us now; V-cycle of 16
+// systems of 64^2 to 176^2 with 4 right-hand sides: 118 us per level, 82 now.
+// ---------------------------------------------------------------------------
+constexpr int TAIL_WG = 1024;
+// Entries per row and rows per thread held in registers, what 128 VGPRs (1024
+// threads) take without spilling: the 5-point stencil of point levels, the
+// 7-point stencil of block levels; 4 rows (4096-row levels) but for FP64 blocks.
+template <int NB>
+constexpr int tail_ml() { return NB == 1 ? 5 : 7; }
+template <typename T, int NB>
+constexpr int tail_tpt() { return sizeof(T) == 8 && NB > 1 ? 2 : 4; }
+
+// LDS elements of a vector of m rows (16-byte ranges)
+template <typename T>
+__host__ __device__ __forceinline__ int tail_range(int m) { return (m + 3) & ~3; }
+
+// Dot products of SELL rows against a vector, streamed 8 entries at a time:
+// acc += sum_k val_k x[col_k - lo], k in order (as spmv_row).
+template <typename T>
+__device__ __forceinline__ T tail_row(const int32_t *__restrict__ scol, const T *__restrict__ sval, int64_t off, int len,
+                                      int lo, const T *x, T acc) {
+    for (int e0 = 0; e0 < len; e0 += 8) {
+        int cc[8];
+        T aa[8], xv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            cc[u] = lo;
+            aa[u] = T(0);
+            if (e0 + u < len) {
+                cc[u] = scol[off + (int64_t)(e0 + u) * 64];
+                aa[u] = sval[off + (int64_t)(e0 + u) * 64];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) xv[u] = x[cc[u] - lo];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (e0 + u < len) acc += aa[u] * xv[u];
+    }
+    return acc;
+}
+
+// The rows of A that a thread owns on a level (row = thread + i * TAIL_WG of
+// the system's m active rows), in registers: values and byte offsets of the
+// columns in x.  Shorter rows are filled up with zeros at the row's own column,
+// threads beyond row m - 1 repeat it.
+template <typename T, int TPT, int ML>
+struct TailRows {
+    T v[TPT][ML];
+    uint32_t c[TPT][ML];   // byte offsets
+    __device__ __forceinline__ void load(const TailLevel &L, int lo, int m) {
+        int64_t off[TPT];
+        int len[TPT];
+#pragma unroll
+        for (int i = 0; i < TPT; ++i) {
+            const int q = lo + min((int)threadIdx.x + i * TAIL_WG, m - 1);
+            // a wavefront's 64 rows lie in at most two slices: scalar loads
+            const int s0 = __builtin_amdgcn_readfirstlane(q >> 6);
+            const int s1 = min(s0 + 1, (lo + m - 1) >> 6);
+            const bool first = (q >> 6) == s0;
+            len[i] = first ? L.slen[s0] : L.slen[s1];
+            off[i] = (first ? L.sptr[s0] : L.sptr[s1]) + (q & 63);
+        }
+        const T *sval = static_cast<const T *>(L.sval);
+#pragma unroll
+        for (int i = 0; i < TPT; ++i) {
+            const int own = min((int)threadIdx.x + i * TAIL_WG, m - 1);
+#pragma unroll
+            for (int u = 0; u < ML; ++u) {
+                int cc = own;
+                v[i][u] = T(0);
+                if (u < len[i]) {
+                    cc = L.scol[off[i] + (int64_t)u * 64] - lo;
+                    v[i][u] = sval[off[i] + (int64_t)u * 64];
+                }
+                c[i][u] = (uint32_t)cc * sizeof(T);
+            }
+        }
+    }
+    __device__ __forceinline__ T dot(int i, const T *x, T acc) const {
+        T xv[ML];
+#pragma unroll
+        for (int u = 0; u < ML; ++u) xv[u] = *reinterpret_cast<const T *>(reinterpret_cast<const unsigned char *>(x) + c[i][u]);
+#pragma unroll
+        for (int u = 0; u < ML; ++u) acc += v[i][u] * xv[u];
+        return acc;
+    }
+};
+
+// x_out = x_in - Lambda res for one row (local index row, NB consecutive lanes
+// per block), res exchanged inside the wavefront through the row's own slot of
+// xout: LDS operations of a wavefront complete in order, and xout is not read
+// as an x by anybody before the next barrier.
+template <typename T, int NB>
+__device__ __forceinline__ void tail_relax(bool valid, int row, T res, T &xo, const T (&lr)[NB], T *xout) {
+    if constexpr (NB == 1) {
+        xo -= lr[0] * res;
+    } else {
+        if (valid) xout[row] = res;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        T rb[NB];
+        const int base = row - row % NB;
+#pragma unroll
+        for (int cc = 0; cc < NB; ++cc) rb[cc] = valid ? xout[base + cc] : T(0);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int cc = 0; cc < NB; ++cc) xo -= lr[cc] * rb[cc];
+    }
+    if (valid) xout[row] = xo;
+}
+
+template <typename T, int NB>
+__device__ __forceinline__ void tail_lam(const T *lam, int lo, int row, int m, T (&lr)[NB]) {
+    const int q = lo + min(row, m - 1);
+    vload<T, NB>(lam + (int64_t)(q / NB) * (NB * NB) + (q % NB) * NB, lr);
+}
+
+// Lambda of sweep q of a visit: the cascade's steps in order, or (rf) in
+// reverse order and transposed.
+template <typename T>
+__device__ __forceinline__ const T *tail_step(const TailLevel &L, int q, int rf) {
+    const int st = q % L.depth, ell = rf ? L.depth - 1 - st : st;
+    return static_cast<const T *>(rf ? L.lamT : L.lam) + (int64_t)ell * L.nbl;
+}
+
+// ns sweeps x_out = x_in - Lambda (A x_in - b) over the rows [0, m) of one
+// level's system, the first reading cur (or from a zero guess) and writing
+// nxt, which then alternate with x and alt; every sweep ends with a barrier.
+// With `res` the residual A x - b of the result is left in alt (no barrier).
+// The thread's rows of A, x and b stay in registers, and the Lambda of a sweep
+// is loaded before the barrier that ends the one before it.
+template <typename T, int NB, int TPT>
+__device__ __forceinline__ void tail_smooth(const TailLevel &L, int lo, int m, const T *b, T *x, T *alt, T *cur, T *nxt,
+                                            int ns, int rf, bool zero, bool res) {
+    TailRows<T, TPT, tail_ml<NB>()> A;
+    A.load(L, lo, m);
+    T lr[TPT][NB], xo[TPT], bv[TPT];
+#pragma unroll
+    for (int i = 0; i < TPT; ++i) {
+        const int row = min((int)threadIdx.x + i * TAIL_WG, m - 1);
+        tail_lam<T, NB>(tail_step<T>(L, 0, rf), lo, row, m, lr[i]);
+        bv[i] = b[row];
+        xo[i] = zero ? T(0) : cur[row];
+    }
+    for (int q = 0; q < ns; ++q) {
+        const T *lam = tail_step<T>(L, q + 1 < ns ? q + 1 : q, rf);
+#pragma unroll
+        for (int i = 0; i < TPT; ++i) {
+            if (i * TAIL_WG < m) {   // uniform
+                const int row = threadIdx.x + i * TAIL_WG;
+                const T r = zero && q == 0 ? -bv[i] : A.dot(i, cur, -bv[i]);
+                tail_relax<T, NB>(row < m, row, r, xo[i], lr[i], nxt);
+                tail_lam<T, NB>(lam, lo, row, m, lr[i]);
+            }
+        }
+        __syncthreads();
+        cur = nxt;
+        nxt = cur == x ? alt : x;
+    }
+    if (res) {
+#pragma unroll
+        for (int i = 0; i < TPT; ++i) {
+            const int row = threadIdx.x + i * TAIL_WG;
+            if (i * TAIL_WG < m && row < m) alt[row] = A.dot(i, x, -bv[i]);
+        }
+    }
+}
+
+// The same sweeps with A streamed from memory.
+template <typename T, int NB>
+__device__ __forceinline__ void tail_smooth_stream(const TailLevel &L, int lo, int m, const T *b, T *x, T *alt, T *cur,
+                                                   T *nxt, int ns, int rf, bool zero, bool res) {
+    const T *sval = static_cast<const T *>(L.sval);
+    for (int q = 0; q < ns; ++q) {
+        const T *lam = tail_step<T>(L, q, rf);
+        for (int r0 = 0; r0 < m; r0 += TAIL_WG) {
+            const int row = r0 + threadIdx.x, g = lo + row;
+            const bool valid = row < m;
+            T lr[NB], r = T(0), xo = T(0);
+            tail_lam<T, NB>(lam, lo, row, m, lr);
+            if (valid) {
+                r = -b[row];
+                if (!(zero && q == 0)) {
+                    r = tail_row<T>(L.scol, sval, L.sptr[g >> 6] + (g & 63), L.slen[g >> 6], lo, cur, r);
+                    xo = cur[row];
+                }
+            }
+            tail_relax<T, NB>(valid, row, r, xo, lr, nxt);
+        }
+        __syncthreads();
+        cur = nxt;
+        nxt = cur == x ? alt : x;
+    }
+    if (res)
+        for (int row = threadIdx.x; row < m; row += TAIL_WG) {
+            const int g = lo + row;
+            alt[row] = tail_row<T>(L.scol, sval, L.sptr[g >> 6] + (g & 63), L.slen[g >> 6], lo, x, -b[row]);
+        }
+}
+
+// One visit's sweeps in the form that the level's rows allow.
+template <typename T, int NB>
+__device__ __forceinline__ void tail_visit(const TailLevel &L, int lo, int m, const T *b, T *x, T *alt, T *cur, T *nxt,
+                                           int ns, int rf, bool zero, bool res) {
+    constexpr int TPT = tail_tpt<T, NB>();
+    if (L.max_len > tail_ml<NB>() || m > TPT * TAIL_WG)
+        tail_smooth_stream<T, NB>(L, lo, m, b, x, alt, cur, nxt, ns, rf, zero, res);
+    else if (m > TAIL_WG)
+        tail_smooth<T, NB, TPT>(L, lo, m, b, x, alt, cur, nxt, ns, rf, zero, res);
+    else
+        tail_smooth<T, NB, 1>(L, lo, m, b, x, alt, cur, nxt, ns, rf, zero, res);
+}
+
+// Rows [a, m) of the system's direct segments: x = A_seg^{-1} b with FP64
+// accumulation, a wavefront per row (as direct_row), four rows at a time.
+template <typename T>
+__device__ __forceinline__ void tail_direct(const TailLevel &L, int lo, int a, int m, const T *b, T *x) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    constexpr int NW = TAIL_WG / 64, U = 4;
+    for (int i0 = a + wv; i0 < m; i0 += NW * U) {
+        double acc[U];
+        const double *row[U];
+        int s[U], n[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            acc[u] = 0.0;
+            const int i = i0 + u * NW;
+            row[u] = L.dinv;
+            s[u] = n[u] = 0;
+            if (i < m) {
+                int p = 0, h = L.nseg - 1;   // segment p with dseg[p] <= lo + i < dseg[p + 1]
+                while (p < h) {
+                    const int mid = (p + h + 1) >> 1;
+                    if (L.dseg[mid] <= lo + i) p = mid;
+                    else h = mid - 1;
+                }
+                s[u] = (int)(L.dseg[p] - lo);
+                n[u] = (int)(L.dseg[p + 1] - L.dseg[p]);
+                row[u] = L.dinv + L.dinv_off[p] + (int64_t)(i - s[u]) * n[u];
+            }
+        }
+        const int nmax = max(max(n[0], n[1]), max(n[2], n[3]));
+        for (int j = lane; j < nmax; j += 64) {
+            double av[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) av[u] = j < n[u] ? row[u][j] : 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (j < n[u]) acc[u] += av[u] * (double)b[s[u] + j];
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc[u] += __shfl_xor(acc[u], off, 64);
+        }
+        if (lane == 0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i0 + u * NW < m) x[i0 + u * NW] = (T)acc[u];
+        }
+    }
+}
+
+// Alg. 1 from tab[0] (its right-hand side in global memory, [n][R]: tab[0].bb,
+// or the FP64 vector b64) to the last entry; the result in tab[0].xb, or x64.  Workgroup (system, right-hand side).
+// sys: [nlev][nsys + 1] row offsets of the systems on every level.  LDS: x and
+// b of every level, then one buffer of the largest level's rows (`alt`): a
+// sweep writes the other one of x and alt, started so that the last one of
+// a visit ends in x.
+template <typename T, int NB>
+__global__ __launch_bounds__(TAIL_WG) void k_tail_vcycle(const TailLevel *__restrict__ tab, int nlev, int nsys,
+                                                         const int32_t *__restrict__ sys, int R, int n_pre,
+                                                         int n_post, int rf, int alt_off,
+                                                         const double *__restrict__ b64, double *__restrict__ x64) {
+    extern __shared__ __align__(16) unsigned char tail_lds[];
+    T *const base = reinterpret_cast<T *>(tail_lds);
+    T *const alt = base + alt_off;
+    const int s = blockIdx.x, k = blockIdx.y;
+    // x_l at x, b_l at x + m (m rows on the level, up to 16-byte ranges)
+    int last = 0;   // the system's last level: nothing of it is smoothed there
+    T *x = base;
+    {
+        const TailLevel &L = tab[0];
+        const int lo = sys[s], m = sys[s + 1] - lo;
+        T *b = x + tail_range<T>(m);
+        const T *gb = static_cast<const T *>(L.bb);
+        for (int r = threadIdx.x; r < m; r += TAIL_WG) {
+            const int64_t e = (int64_t)(lo + r) * R + k;
+            b[r] = b64 ? (T)b64[e] : gb[e];
+        }
+        __syncthreads();
+    }
+    for (int l = 0;; ++l) {
+        const TailLevel &L = tab[l];
+        const int lo = sys[l * (nsys + 1) + s], m = sys[l * (nsys + 1) + s + 1] - lo;
+        const int act = max(0, min((int)L.n_active - lo, m));
+        T *b = x + tail_range<T>(m);
+        tail_direct<T>(L, lo, act, m, b, x);   // reads b only
+        if (l + 1 == nlev || act == 0) {
+            last = l;
+            __syncthreads();
+            break;
+        }
+        const int ns = n_pre * L.depth;
+        tail_visit<T, NB>(L, lo, act, b, x, alt, x, (ns & 1) ? x : alt, ns, rf, true, true);   // ends in x
+        __syncthreads();
+        const int mc = sys[(l + 1) * (nsys + 1) + s + 1] - sys[(l + 1) * (nsys + 1) + s];
+        T *xn = b + tail_range<T>(m), *bn = xn + tail_range<T>(mc);
+        const T rs = (T)L.r_scale;
+        for (int I = threadIdx.x; I < mc; I += TAIL_WG) {
+            T v = T(0);
+            if (L.agg_k > 0) {
+                for (int u = 0; u < L.agg_k; ++u) v += alt[I * L.agg_k + u];
+            } else {
+                v = tail_row<T>(L.tcol, static_cast<const T *>(L.tval), L.tptr[I >> 6] + (I & 63), L.tlen[I >> 6], 0,
+                                alt, v);
+            }
+            bn[I] = v * rs;
+        }
+        __syncthreads();
+        x = xn;
+    }
+    for (int l = last - 1; l >= 0; --l) {
+        const TailLevel &L = tab[l];
+        const int lo = sys[l * (nsys + 1) + s], m = sys[l * (nsys + 1) + s + 1] - lo;
+        const int act = max(0, min((int)L.n_active - lo, m));
+        const T *xc = x;
+        T *b = x - tail_range<T>(m);
+        x = b - tail_range<T>(m);
+        const int ns = n_post * L.depth;
+        T *cur = (ns & 1) ? alt : x;
+        const int sh = L.agg_k > 0 ? __builtin_ctz((unsigned)L.agg_k) : 0;   // agg_k divides 64
+        for (int row = threadIdx.x; row < act; row += TAIL_WG) {
+            T v = x[row];
+            if (L.agg_k > 0) v -= xc[row >> sh];
+            else
+                v -= tail_row<T>(L.pcol, static_cast<const T *>(L.pval), L.pptr[row >> 6] + (row & 63),
+                                 L.plen[row >> 6], 0, xc, T(0));
+            cur[row] = v;
+        }
+        __syncthreads();
+        tail_visit<T, NB>(L, lo, act, b, x, alt, cur, cur == x ? alt : x, ns, 0, false, false);
+    }
+    const int lo = sys[s], m = sys[s + 1] - lo;
+    T *gx = static_cast<T *>(tab[0].xb);
+    for (int r = threadIdx.x; r < m; r += TAIL_WG) {
+        const int64_t e = (int64_t)(lo + r) * R + k;
+        if (x64) x64[e] = (double)x[r];
+        else gx[e] = x[r];
+    }
+}
+
+template <class F>
+void tail_dispatch(int nb, F &&f) {
+    switch (nb) {
+        case 1: f(std::integral_constant<int, 1>{}); break;
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        case 8: f(std::integral_constant<int, 8>{}); break;
+        default: fail(CS_EINVAL, "tail block size must be 1, 2, 4 or 8");
+    }
+}
+
+template <typename T>
+const T *pick(const DBuf<double> &d, const DBuf<float> &f) {
+    if constexpr (std::is_same<T, double>::value) return d.get();
+    else return f.get();
+}
+
+}  // namespace
+
+namespace {
+
+// Dynamic LDS that a workgroup may use (160 KB per CU on gfx950).
+int64_t tail_lds_limit(const Ctx &c) {
+    int v = 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, c.device) != hipSuccess) return 65536;
+    return v;
+}
+
+// Row offsets of the independent systems on every level, [level][nsys + 1]: a
+// batch under aggregation splits as its finest level does, provided that no
+// row of levels >= from couples two systems; anything else is one system.
+std::vector<std::vector<int32_t>> tail_systems(const Ctx &c, int from) {
+    const int nl = (int)c.lv.size();
+    std::vector<std::vector<int32_t>> rng(nl);
+    bool split = c.sys_ptr.size() > 2;
+    if (split) rng[0].assign(c.sys_ptr.begin(), c.sys_ptr.end());
+    for (int l = 0; split && l + 1 < nl; ++l) {
+        const Level &L = c.lv[l];
+        split = c.fuse_transfers && L.agg_k > 0;
+        for (size_t q = 0; split && q < rng[l].size(); ++q) {
+            const int64_t r = std::min<int64_t>(rng[l][q], L.n_active);
+            split = r % L.agg_k == 0;
+            rng[l + 1].push_back((int32_t)(r / std::max(L.agg_k, 1)));
+        }
+        split = split && rng[l + 1].back() == c.lv[l + 1].n;
+    }
+    for (int l = from; split && l < nl; ++l) {
+        const Level &L = c.lv[l];
+        for (size_t q = 0; split && q + 1 < rng[l].size(); ++q) {
+            const int32_t r0 = rng[l][q], r1 = rng[l][q + 1];
+            split = r0 % L.nb == 0;
+            for (int64_t e = L.h_ptr[r0]; split && e < L.h_ptr[r1]; ++e) split = L.h_col[e] >= r0 && L.h_col[e] < r1;
+            for (size_t t = 0; split && t + 1 < L.dseg.size(); ++t)   // a segment belongs to one system
+                split = !(L.dseg[t] < r1 && L.dseg[t + 1] > r0) || (L.dseg[t] >= r0 && L.dseg[t + 1] <= r1);
+        }
+    }
+    if (!split)
+        for (int l = 0; l < nl; ++l) rng[l] = {0, (int32_t)c.lv[l].n};
+    return rng;
+}
+
+// LDS elements of the tail from level `from` for its largest system: x and b
+// of every level (in *alt), and the buffer of the largest level after them.
+int64_t tail_elements(const std::vector<std::vector<int32_t>> &rng, int from, int64_t *alt) {
+    int64_t xb = 0, top = 0;
+    for (size_t s = 0; s + 1 < rng[0].size(); ++s) {
+        int64_t t = 0;
+        for (size_t l = from; l < rng.size(); ++l) {
+            const int64_t m = tail_range<float>(rng[l][s + 1] - rng[l][s]);
+            t += 2 * m;
+            top = std::max(top, m);
+        }
+        xb = std::max(xb, t);
+    }
+    if (alt) *alt = xb;
+    return xb + top;
+}
+
+}  // namespace
+
+// The levels the tail kernel covers: the first level l (the finest included)
+// from which every level has at most c.tail_rows rows, every smoothed one is
+// additive (no overlapping blocks) with one common block size of 1, 2, 4 or 8,
+// the cycle pre- and post-smooths, and a system's vectors on all covered levels
+// fit a workgroup's LDS; -1 when there is none.
+int tail_start(const Ctx &c) {
+    const int nl = (int)c.lv.size();
+    if (c.tail_rows <= 0 || nl < 2 || c.opt.mode != CS_ADDITIVE || c.opt.n_pre < 1 || c.opt.n_post < 1) return -1;
+    const int64_t nb = c.lv[nl - 2].nb;
+    if (nb != 1 && nb != 2 && nb != 4 && nb != 8) return -1;
+    int from = -1;
+    for (int l = nl - 1; l >= 0; --l) {
+        const Level &V = c.lv[l];
+        bool ok = V.n <= c.tail_rows && !V.ovl_m;
+        if (l + 1 < nl) ok = ok && V.depth >= 1 && V.nb == nb && V.n_active > 0;
+        if (!ok) break;
+        from = l;
+    }
+    if (from < 0 || from >= nl - 1) return -1;
+    const auto rng = tail_systems(c, from);
+    const int64_t es = c.precision == CS_FP64 ? 8 : 4, lim = tail_lds_limit(c);
+    while (from < nl - 1 && tail_elements(rng, from, nullptr) * es > lim) ++from;
+    return from < nl - 1 ? from : -1;
+}
+
+namespace {
+
+template <typename T>
+void tail_table(Ctx &c, int nrhs) {
+    if (c.tail_gen == c.gen && c.tail_prec == c.precision && c.tail_nrhs == nrhs) return;
+    const int from = tail_start(c);
+    c.tail_from = from;
+    if (from < 0) return;
+    const auto rng = tail_systems(c, from);
+    std::vector<TailLevel> tab;
+    std::vector<int32_t> sys;
+    const double es = sizeof(T), vr = (double)nrhs * es;
+    double bytes = 0.0;
+    for (size_t l = from; l < c.lv.size(); ++l) {
+        const Level &L = c.lv[l];
+        const bool agg = c.fuse_transfers && L.agg_k > 0;
+        sys.insert(sys.end(), rng[l].begin(), rng[l].end());
+        bytes += (double)L.dinv.n * 8.0 + 2.0 * (L.n - L.n_active) * vr;
+        TailLevel t{};
+        if (l + 1 < c.lv.size()) {
+            const double A = L.act_nnz * (es + 4.0), lamb = (double)L.n_active * L.nb * es;
+            const double v = (double)L.n_active * vr, sweeps = (double)(c.opt.n_pre + c.opt.n_post) * L.depth;
+            bytes += (lamb + 2.0 * v) + (sweeps - 1.0) * (A + lamb + 3.0 * v);   // the first from zero
+            bytes += A + 2.0 * v + 2.0 * (double)L.nc * vr + (agg ? 0.0 : 2.0 * L.p_nnz * (es + 4.0));   // transfers
+            t.lam = pick<T>(L.lam64, L.lam32);
+            t.lamT = pick<T>(L.lam64T, L.lam32T);
+            for (int64_t r = 0; r < L.n_active; ++r)
+                t.max_len = std::max(t.max_len, (int)(L.h_ptr[r + 1] - L.h_ptr[r]));
+            if (!agg) {
+                t.pptr = L.psell.slice_ptr.get();
+                t.plen = L.psell.slice_len.get();
+                t.pcol = L.psell.col.get();
+                t.pval = pick<T>(L.psell.val64, L.psell.val32);
+                t.tptr = L.ptsell.slice_ptr.get();
+                t.tlen = L.ptsell.slice_len.get();
+                t.tcol = L.ptsell.col.get();
+                t.tval = pick<T>(L.ptsell.val64, L.ptsell.val32);
+            }
+        }
+        t.n_active = L.n_active;
+        t.nbl = L.B * L.nb * L.nb;
+        t.sptr = L.sell.slice_ptr.get();
+        t.slen = L.sell.slice_len.get();
+        t.scol = L.sell.col.get();
+        t.sval = pick<T>(L.sell.val64, L.sell.val32);
+        t.bb = L.w_bb;
+        t.xb = L.w_xb;
+        t.depth = L.depth;
+        t.agg_k = agg ? L.agg_k : 0;
+        t.r_scale = L.r_scale;
+        t.nseg = L.dseg.size() > 1 ? (int)L.dseg.size() - 1 : 0;
+        t.dseg = L.dseg_d.get();
+        t.dinv_off = L.dinv_off.get();
+        t.dinv = L.dinv.get();
+        tab.push_back(t);
+    }
+    int64_t alt = 0;
+    c.tail_lds = tail_elements(rng, from, &alt) * sizeof(T);
+    c.tail_alt = (int)alt;
+    c.tail_nsys = (int)rng[from].size() - 1;
+    c.tail_host = tab;
+    c.tail_sys_host = sys;
+    c.tail_bytes = bytes;
+    c.tail_tab.upload(c.tail_host.data(), c.tail_host.size(), c.stream);
+    c.tail_sys.upload(c.tail_sys_host.data(), c.tail_sys_host.size(), c.stream);
+    tail_dispatch((int)c.lv[from].nb, [&](auto nbc) {
+        constexpr int NB = decltype(nbc)::value;
+        CS_HIP(   // more than 64 KB of dynamic LDS has to be asked for
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_tail_vcycle<T, NB>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.tail_lds));
+    });
+    c.tail_gen = c.gen;
+    c.tail_prec = c.precision;
+    c.tail_nrhs = nrhs;
+}
+
+template <typename T>
+void launch(Ctx &c, int nrhs, const double *b64, double *x64) {
+    hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    (void)trace_begin_launch(c, CS_TRACE_TAIL, c.tail_bytes, &ev0, &ev1);
+    tail_dispatch((int)c.lv[c.tail_from].nb, [&](auto nbc) {
+        constexpr int NB = decltype(nbc)::value;
+        hipExtLaunchKernelGGL((k_tail_vcycle<T, NB>), dim3(c.tail_nsys, nrhs), dim3(TAIL_WG), (unsigned)c.tail_lds,
+                              c.stream, ev0, ev1, 0, (const TailLevel *)c.tail_tab.get(),
+                              (int)c.lv.size() - c.tail_from, c.tail_nsys, (const int32_t *)c.tail_sys.get(), nrhs,
+                              c.opt.n_pre, c.opt.n_post, c.opt.order == CS_RF ? 1 : 0, c.tail_alt, b64, x64);
+    });
+    CS_LAUNCH_CHECK();
+}
+
+}  // namespace
+
+// Build the table of the covered levels for the current workspace (kept until
+// the buffers, the precision, the right-hand sides or the limit change).
+void tail_prepare(Ctx &c, int nrhs) {
+    if (c.precision == CS_FP64) tail_table<double>(c, nrhs);
+    else tail_table<float>(c, nrhs);
+}
+
+// The V-cycle from level c.tail_from down, in one launch; with b64 and x64 from
+// and into those FP64 vectors instead of the level's workspace.
+void tail_launch(Ctx &c, int nrhs, const double *b64, double *x64) {
+    if (c.precision == CS_FP64) launch<double>(c, nrhs, b64, x64);
+    else launch<float>(c, nrhs, b64, x64);
+}
+
+}  // namespace cs

@@ -175,3 +175,49 @@ def test_autotune_picks_the_fastest_tail(gpu_lib):
     assert i1["iterations"] == i0["iterations"]
     np.testing.assert_array_equal(x1.cpu().numpy(), x0.cpu().numpy())
     s.close()
+
+
+@pytest.mark.parametrize("family,n,nrhs,precision", [
+    ("multiphase3d", 16, 2, "fp64"),    # 27-point rows (streamed), trilinear transfers, blocks of 8
+    ("multiphase3d", 12, 1, "fp32"),
+    ("stokes", 32, 1, "fp32"),          # saddle point, blocks of 4, up to 15 entries per row
+    ("stokes", 24, 4, "fp64"),
+    ("lognormal", 72, 8, "fp64"),       # 5184 rows: more than the registers hold, odd bottom (9^2)
+    ("lognormal", 80, 1, "fp32"),
+    ("interface", 28, 8, "fp32"),       # 21952 rows do not fit: starts at 2744, odd bottom (7^3)
+    ("interface", 20, 2, "fp64"),
+    ("poisson", 16, 1, "fp64"),         # a single tile per level
+])
+def test_tail_general_transfers_and_sizes(gpu_lib, family, n, nrhs, precision):
+    """Hierarchies with general transfers, rows longer than the kernel holds in
+    registers, row counts off its tiles and levels beyond the LDS."""
+    from synth import fe, stokes
+    rng = np.random.default_rng(n)
+    levels = {"multiphase3d": lambda: fe.multiphase3d(n).levels, "stokes": lambda: stokes.mac2d(n).levels,
+              "lognormal": lambda: fd.lognormal2d(n).levels, "interface": lambda: fd.interface3d(n).levels,
+              "poisson": lambda: fd.poisson2d(n).levels}[family]()
+    b = rng.standard_normal((levels[0].n, nrhs))
+    s = gpu_lib.Solver(levels)
+    s.setup(depth=3, order="FF" if family == "stokes" else "RF", n_pre=2, precision=precision)
+    s.set_tail(65536)
+    m, first = s.tail()
+    assert m == 65536 and 0 <= first < len(levels) - 1
+    x1 = s.vcycle(b).cpu().numpy()
+    s.set_tail(0)
+    np.testing.assert_array_equal(s.vcycle(b).cpu().numpy(), x1)
+    s.close()
+
+
+def test_tail_systems_of_ragged_sizes(gpu_lib):
+    """A batch whose systems' rows straddle slices and end on different levels,
+    each in its own workgroup, and the same rows declared one system."""
+    bt = concatenate(fd.lognormal_batch(5, nrhs=2, sizes=[24, 40, 16, 56, 8], config_id=15))
+    s = gpu_lib.Solver(bt.levels)
+    s.setup(depth=2, precision="fp64")
+    x0 = s.vcycle(bt.rhs).cpu().numpy()
+    for sys_ptr in (None, bt.sys_ptr):
+        s.set_systems(sys_ptr)
+        s.set_tail(65536)
+        assert s.tail()[1] >= 0
+        np.testing.assert_array_equal(s.vcycle(bt.rhs).cpu().numpy(), x0)
+    s.close()
