@@ -1,6 +1,8 @@
 // Block-smoother network: FP32 GEMMs on the matrix cores (v_mfma_f32_16x16x4f32)
 // with fused bias / SiLU / SiLU-derivative / output-scaling epilogues, MSE
-// loss, Adam, and the Q1 block features.  See cascade_learned.h.
+// loss, Adam, and the Q1 block features.  See cascade_learned.h.  Networks of
+// widths up to 128 run the row-tile path of mlp_rows.hip; the products here
+// serve the others (rows_path says which).
 #include <algorithm>
 #include <cmath>
 
@@ -456,6 +458,10 @@ void backward(Mlp &m, hipStream_t s, const float *X, const int32_t *rows, int64_
 }  // namespace
 
 void mlp_predict(Mlp &m, hipStream_t s, const float *X, int64_t n, float *Y) {
+    if (rows_path(m, X)) {
+        rows_predict(m, s, X, n, Y);
+        return;
+    }
     ensure_cap(m, std::min<int64_t>(std::max<int64_t>(n, 1), CHUNK));
     for (int64_t r0 = 0; r0 < n; r0 += CHUNK) {
         const int64_t nr = std::min<int64_t>(CHUNK, n - r0);
@@ -560,7 +566,9 @@ cs_status cs_mlp_param_count(cs_mlp h, int64_t *count) {
 cs_status cs_mlp_set_params(cs_mlp h, const float *params) {
     return mguarded(h, [&](Mlp &m) {
         mneed(params != nullptr, "null parameters");
-        for (int64_t e = 0; e < m.np; ++e) mneed(std::isfinite(params[e]), "parameters must be finite");
+        bool finite = true;
+        for (int64_t e = 0; e < m.np; ++e) finite &= std::isfinite(params[e]);
+        mneed(finite, "parameters must be finite");
         m.p.upload(params, m.np, m.stream);
         CS_HIP(hipMemsetAsync(m.m.get(), 0, m.m.bytes(), m.stream));
         CS_HIP(hipMemsetAsync(m.v.get(), 0, m.v.bytes(), m.stream));
@@ -610,10 +618,14 @@ cs_status cs_mlp_gradient(cs_mlp h, const float *X, const float *T, const int32_
                           double *loss) {
     return mguarded(h, [&](Mlp &m) {
         mneed(X && T && grad && loss && n > 0 && n <= (1 << 24), "bad gradient arguments");
-        cs::ensure_cap(m, n);
-        cs::forward(m, m.stream, X, rows, n, false, m.y.get());
-        cs::mse(m, m.stream, T, rows, n, true, 0, false);
-        cs::backward(m, m.stream, X, rows, n);
+        if (cs::rows_path(m, X)) {
+            cs::rows_gradient(m, m.stream, X, T, rows, n);
+        } else {
+            cs::ensure_cap(m, n);
+            cs::forward(m, m.stream, X, rows, n, false, m.y.get());
+            cs::mse(m, m.stream, T, rows, n, true, 0, false);
+            cs::backward(m, m.stream, X, rows, n);
+        }
         m.g.download(grad, m.np, m.stream);
         CS_HIP(hipMemcpyAsync(m.h_acc, m.acc.get(), sizeof(double), hipMemcpyDeviceToHost, m.stream));
         CS_HIP(hipStreamSynchronize(m.stream));
@@ -624,14 +636,18 @@ cs_status cs_mlp_gradient(cs_mlp h, const float *X, const float *T, const int32_
 cs_status cs_mlp_loss(cs_mlp h, const float *X, const float *T, const int32_t *rows, int64_t n, double *loss) {
     return mguarded(h, [&](Mlp &m) {
         mneed(X && T && loss && n > 0, "bad loss arguments");
-        cs::ensure_cap(m, std::min<int64_t>(n, cs::CHUNK));
-        for (int64_t r0 = 0; r0 < n; r0 += cs::CHUNK) {
-            const int64_t nr = std::min<int64_t>(cs::CHUNK, n - r0);
-            const float *Xc = rows ? X : X + r0 * m.n_in;
-            const float *Tc = rows ? T : T + r0 * m.n_out;
-            const int32_t *rc = rows ? rows + r0 : nullptr;
-            cs::forward(m, m.stream, Xc, rc, nr, false, m.y.get());
-            cs::mse(m, m.stream, Tc, rc, nr, false, 0, r0 > 0);
+        if (cs::rows_path(m, X)) {
+            cs::rows_loss(m, m.stream, X, T, rows, n);
+        } else {
+            cs::ensure_cap(m, std::min<int64_t>(n, cs::CHUNK));
+            for (int64_t r0 = 0; r0 < n; r0 += cs::CHUNK) {
+                const int64_t nr = std::min<int64_t>(cs::CHUNK, n - r0);
+                const float *Xc = rows ? X : X + r0 * m.n_in;
+                const float *Tc = rows ? T : T + r0 * m.n_out;
+                const int32_t *rc = rows ? rows + r0 : nullptr;
+                cs::forward(m, m.stream, Xc, rc, nr, false, m.y.get());
+                cs::mse(m, m.stream, Tc, rc, nr, false, 0, r0 > 0);
+            }
         }
         CS_HIP(hipMemcpyAsync(m.h_acc, m.acc.get(), sizeof(double), hipMemcpyDeviceToHost, m.stream));
         CS_HIP(hipStreamSynchronize(m.stream));
@@ -645,26 +661,35 @@ cs_status cs_mlp_train(cs_mlp h, const float *X, const float *T, const int32_t *
         mneed(X && T && order && n_train > 0 && epochs >= 1 && batch >= 1 && batch <= (1 << 20), "bad training "
                                                                                                    "arguments");
         mneed(lr0 > 0 && lr_min >= 0 && lr_min <= lr0, "bad learning rates");
-        cs::ensure_cap(m, std::min<int64_t>(batch, n_train));
+        const bool tiles = cs::rows_path(m, X);
+        if (!tiles) cs::ensure_cap(m, std::min<int64_t>(batch, n_train));
         const int64_t steps = cs::ceil_div(n_train, batch);
         cs::ensure_acc(m, (size_t)steps);
         const int64_t total = steps * epochs;
         const double b1 = 0.9, b2 = 0.999;
         int64_t k = 0;
+        auto rate = [&]() {   // of the next step
+            ++m.step;
+            const double lr = lr_min + 0.5 * (lr0 - lr_min) * (1.0 + std::cos(3.14159265358979323846 * (double)k++ / (double)total));
+            return cs::AdamRate{(float)lr, (float)b1, (float)b2, 1e-8f,
+                                (float)(1.0 / (1.0 - std::pow(b1, (double)m.step))),
+                                (float)(1.0 / (1.0 - std::pow(b2, (double)m.step)))};
+        };
         for (int ep = 0; ep < epochs; ++ep) {
             const int32_t *ord = order + (int64_t)ep * n_train;
-            for (int64_t st = 0; st < steps; ++st, ++k) {
-                const int64_t r0 = st * batch, nr = std::min<int64_t>(batch, n_train - r0);
-                cs::forward(m, m.stream, X, ord + r0, nr, false, m.y.get());
-                cs::mse(m, m.stream, T, ord + r0, nr, true, (int)st, false);
-                cs::backward(m, m.stream, X, ord + r0, nr);
-                ++m.step;
-                const double lr = lr_min + 0.5 * (lr0 - lr_min) * (1.0 + std::cos(3.14159265358979323846 * (double)k / (double)total));
-                const float c1 = (float)(1.0 / (1.0 - std::pow(b1, (double)m.step)));
-                const float c2 = (float)(1.0 / (1.0 - std::pow(b2, (double)m.step)));
-                hipLaunchKernelGGL(cs::k_adam, dim3(cs::gdim(m.np)), dim3(cs::WG), 0, m.stream, m.np, m.p.get(),
-                                   m.g.get(), m.m.get(), m.v.get(), (float)lr, (float)b1, (float)b2, 1e-8f, c1, c2);
-                CS_LAUNCH_CHECK();
+            if (tiles) {
+                cs::rows_epoch(m, m.stream, X, T, ord, n_train, batch, rate);
+            } else {
+                for (int64_t st = 0; st < steps; ++st) {
+                    const int64_t r0 = st * batch, nr = std::min<int64_t>(batch, n_train - r0);
+                    cs::forward(m, m.stream, X, ord + r0, nr, false, m.y.get());
+                    cs::mse(m, m.stream, T, ord + r0, nr, true, (int)st, false);
+                    cs::backward(m, m.stream, X, ord + r0, nr);
+                    const cs::AdamRate r = rate();
+                    hipLaunchKernelGGL(cs::k_adam, dim3(cs::gdim(m.np)), dim3(cs::WG), 0, m.stream, m.np, m.p.get(),
+                                       m.g.get(), m.m.get(), m.v.get(), r.lr, r.b1, r.b2, r.eps, r.c1, r.c2);
+                    CS_LAUNCH_CHECK();
+                }
             }
             CS_HIP(hipMemcpyAsync(m.h_acc, m.acc.get(), steps * sizeof(double), hipMemcpyDeviceToHost, m.stream));
             CS_HIP(hipStreamSynchronize(m.stream));

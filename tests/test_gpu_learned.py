@@ -76,6 +76,36 @@ def test_gradient_matches_oracle(gpu_lib, L, n_in, width, n_out, n):
     assert net.loss(X, T, rows) == pytest.approx(ol, rel=1e-5)
 
 
+# the row-tile path's edges (16-, 32- and 64-row tiles, 64-row product tiles,
+# 16-deep slices, padded widths up to 128): one row, one less and one more than a
+# tile, the switch to larger tiles, sums over many row slices
+ROW_SHAPES = [(4, 4, 1, 1), (20, 64, 127, 15), (1464, 128, 128, 17), (64, 68, 2, 63), (132, 128, 5, 65),
+              (1464, 20, 128, 1024), (16, 124, 128, 16384), (8, 128, 3, 16385), (260, 36, 7, 33001)]
+
+
+@pytest.mark.parametrize("n_in,width,n_out,n", ROW_SHAPES)
+def test_row_tiles_match_oracle(gpu_lib, L, n_in, width, n_out, n):
+    test_forward_matches_oracle(gpu_lib, L, n_in, width, n_out, n)
+    test_gradient_matches_oracle(gpu_lib, L, n_in, width, n_out, n)
+
+
+def test_row_tiles_match_the_general_products(gpu_lib, L):
+    """The same network on rows that start off a 16-byte boundary, which the
+    general products take: equal within the rounding of the two sums."""
+    import torch
+    X, T, rng = random_case(36, 32, 9, 101, 5)
+    net = L.Mlp(36, 32, 9)
+    net.init_params(seed=11)
+    buf = torch.empty(101 * 36 + 1, device="cuda")
+    off = buf[1:].view(101, 36)
+    off.copy_(torch.as_tensor(X))
+    assert off.data_ptr() % 16
+    assert rel(net.forward(off).cpu().numpy(), net.forward(X).cpu().numpy()) <= 1e-5
+    (ga, la), (gb, lb) = net.gradient(off, T), net.gradient(X, T)
+    assert rel(ga, gb) <= 1e-4 and la == pytest.approx(lb, rel=1e-5)
+    assert net.loss(off, T) == pytest.approx(net.loss(X, T), rel=1e-5)
+
+
 def test_adam_training_matches_oracle_loop(gpu_lib, L):
     """Two epochs of mini-batch Adam with the cosine rate (ragged last batch)
     against the same loop in FP64.  The first Adam steps move every weight by
