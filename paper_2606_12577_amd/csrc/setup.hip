@@ -16,29 +16,15 @@
 #include <type_traits>
 
 #include "cs_internal.h"
+#include "fit_device.h"
 
 namespace cs {
 
 namespace {
 
-constexpr int WG = 256;
 constexpr int UNION_CAP = 4096;   // candidate columns per row in the symbolic step (a power of two)
 constexpr int UNION_CAP_BIG = 8192;   // the same for wide rows (32 KB of LDS; a power of two: the sort pads to one)
 constexpr int MATCH_CAP = 8192;   // (column, neighbour) matches cached per row
-constexpr int MAXNB = 16;
-constexpr double PIVOT_TOL = 1e-13;
-
-__device__ inline int bsearch_i32(const int32_t *a, int lo, int hi, int32_t key) {
-    // index of key in the sorted range a[lo, hi), or -1
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        int32_t v = a[mid];
-        if (v == key) return mid;
-        if (v < key) lo = mid + 1;
-        else hi = mid;
-    }
-    return -1;
-}
 
 // ---------------------------------------------------------------------------
 // prescaling
@@ -630,178 +616,6 @@ __global__ __launch_bounds__(WGS, NB <= 8 ? 6 * (WG / WGS) : 1) void k_rowprod_n
     }
 }
 
-// Lambda~ (G + tau I) = H for one block (G, H: nb x nb in LDS, row-major), by
-// the whole workgroup, tau = ridge tr(G) / nb (ridge = 0: the plain normal
-// equations; ridge > 0: the Tikhonov-regularised fit).  Lc and V are LDS
-// scratch of MAXNB^2 doubles.  Writes Lambda~ to out and, from thread 0,
-// whether the matrix was (numerically) singular to *singular.
-__device__ void normal_solve(const double *G, const double *H, double *Lc, double *V, int nb,
-                             double *__restrict__ out, int32_t *__restrict__ singular, double ridge) {
-    const int t = threadIdx.x;
-    const int nb2 = nb * nb;
-    double trace = 0.0;
-    for (int q = 0; q < nb; ++q) trace += G[q * nb + q];
-    const double tau = ridge > 0.0 ? ridge * trace / nb : 0.0;
-    // Lambda~ G = H.  Regular G: Gauss-Jordan inverse of [G | I] (G is SPD:
-    // no pivoting; the pivots are the Cholesky pivots squared, with the same
-    // cut-off), one thread per entry, two barriers per step.  A pivot below
-    // PIVOT_TOL max diag(G) marks G as (numerically) singular: then the
-    // minimum-norm solution through a parallel cyclic Jacobi eigen-decomposition.
-    __shared__ double Aug[MAXNB * 2 * MAXNB];
-    const int w2 = 2 * nb;
-    double dmax = 0.0;
-    for (int q = 0; q < nb; ++q) dmax = fmax(dmax, G[q * nb + q] + tau);
-    bool bad = !(dmax > 0.0);
-    for (int e = t; e < nb * w2; e += WG) {
-        const int r = e / w2, c = e % w2;
-        Aug[e] = c < nb ? G[r * nb + c] + (r == c ? tau : 0.0) : (c - nb == r ? 1.0 : 0.0);
-    }
-    __syncthreads();
-    constexpr int PER = (MAXNB * 2 * MAXNB + WG - 1) / WG;
-    for (int q = 0; q < nb && !bad; ++q) {
-        const double piv = Aug[q * w2 + q];
-        if (!(piv > PIVOT_TOL * dmax)) {   // same value in every thread: uniform
-            bad = true;
-            break;
-        }
-        double f[PER], g[PER];
-#pragma unroll
-        for (int k2 = 0; k2 < PER; ++k2) {
-            const int e = t + k2 * WG;
-            if (e < nb * w2) {
-                f[k2] = Aug[(e / w2) * w2 + q];
-                g[k2] = Aug[q * w2 + e % w2];
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k2 = 0; k2 < PER; ++k2) {
-            const int e = t + k2 * WG;
-            if (e < nb * w2) Aug[e] = (e / w2 == q) ? g[k2] / piv : Aug[e] - f[k2] * g[k2] / piv;
-        }
-        __syncthreads();
-    }
-    if (t == 0) *singular = bad ? 1 : 0;
-    if (!bad) {
-        if (t < nb2) {
-            const int r = t / nb, c = t % nb;
-            double acc = 0.0;
-            for (int u = 0; u < nb; ++u) acc += H[r * nb + u] * Aug[u * w2 + nb + c];
-            out[t] = acc;
-        }
-        return;
-    }
-    // ---- (near-)singular G: Lambda~ = H V diag(1/ev, ev kept) V^T
-    const int m = nb + (nb & 1);   // even order for the round-robin pairing (zero padding)
-    __shared__ int pp_s[MAXNB / 2], pq_s[MAXNB / 2], pair_of[MAXNB], side_of[MAXNB];
-    __shared__ double rc_s[MAXNB / 2], rs_s[MAXNB / 2], off_s[WG], dia_s[WG];
-    for (int e = t; e < m * m; e += WG) {
-        const int r = e / m, c = e % m;
-        Lc[e] = (r < nb && c < nb) ? G[r * nb + c] + (r == c ? tau : 0.0) : 0.0;
-        V[e] = r == c ? 1.0 : 0.0;
-    }
-    __syncthreads();
-    for (int sweep = 0; sweep < 40; ++sweep) {
-        double off = 0.0, dia = 0.0;
-        for (int e = t; e < m * m; e += WG) {
-            const double v = Lc[e];
-            if (e / m == e % m) dia += v * v;
-            else off += v * v;
-        }
-        off_s[t] = off;
-        dia_s[t] = dia;
-        __syncthreads();
-        for (int h = WG / 2; h > 0; h >>= 1) {
-            if (t < h) {
-                off_s[t] += off_s[t + h];
-                dia_s[t] += dia_s[t + h];
-            }
-            __syncthreads();
-        }
-        const double offt = off_s[0], diat = dia_s[0];
-        __syncthreads();
-        if (offt <= 1e-30 * diat || offt == 0.0) break;   // uniform
-        for (int k = 0; k < m - 1; ++k) {
-            // circle-method pairing: (m-1, k) and ((k+j) mod (m-1), (k-j) mod (m-1))
-            if (t < m / 2) {
-                int a1, b1;
-                if (t == 0) {
-                    a1 = m - 1;
-                    b1 = k;
-                } else {
-                    a1 = (k + t) % (m - 1);
-                    b1 = (k - t + (m - 1)) % (m - 1);
-                }
-                const int pp = min(a1, b1), qq = max(a1, b1);
-                pp_s[t] = pp;
-                pq_s[t] = qq;
-                pair_of[pp] = t;
-                side_of[pp] = 0;
-                pair_of[qq] = t;
-                side_of[qq] = 1;
-                const double apq = Lc[pp * m + qq];
-                double c = 1.0, sn = 0.0;
-                if (apq != 0.0) {
-                    const double tau = (Lc[qq * m + qq] - Lc[pp * m + pp]) / (2.0 * apq);
-                    const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                    c = 1.0 / sqrt(1.0 + tt * tt);
-                    sn = tt * c;
-                }
-                rc_s[t] = c;
-                rs_s[t] = sn;
-            }
-            __syncthreads();
-            // rows: Lc <- J^T Lc
-            double nv[(MAXNB * MAXNB + WG - 1) / WG];
-            for (int e = t, k2 = 0; e < m * m; e += WG, ++k2) {
-                const int r = e / m, c2 = e % m, pr = pair_of[r];
-                const double c = rc_s[pr], sn = rs_s[pr];
-                const double vp = Lc[pp_s[pr] * m + c2], vq = Lc[pq_s[pr] * m + c2];
-                nv[k2] = side_of[r] == 0 ? c * vp - sn * vq : sn * vp + c * vq;
-            }
-            __syncthreads();
-            for (int e = t, k2 = 0; e < m * m; e += WG, ++k2) Lc[e] = nv[k2];
-            __syncthreads();
-            // columns: Lc <- Lc J, V <- V J
-            double nw[(MAXNB * MAXNB + WG - 1) / WG];
-            for (int e = t, k2 = 0; e < m * m; e += WG, ++k2) {
-                const int r = e / m, c2 = e % m, pr = pair_of[c2];
-                const double c = rc_s[pr], sn = rs_s[pr];
-                const int p0 = pp_s[pr], q0 = pq_s[pr];
-                const double lp = Lc[r * m + p0], lq = Lc[r * m + q0];
-                const double vp = V[r * m + p0], vq = V[r * m + q0];
-                nv[k2] = side_of[c2] == 0 ? c * lp - sn * lq : sn * lp + c * lq;
-                nw[k2] = side_of[c2] == 0 ? c * vp - sn * vq : sn * vp + c * vq;
-            }
-            __syncthreads();
-            for (int e = t, k2 = 0; e < m * m; e += WG, ++k2) {
-                Lc[e] = nv[k2];
-                V[e] = nw[k2];
-            }
-            __syncthreads();
-        }
-    }
-    double emax = 0.0;
-    for (int q = 0; q < nb; ++q) emax = fmax(emax, fabs(Lc[q * m + q]));
-    // HV[r][a] = sum_u H[r][u] V[u][a] (into Aug)
-    if (t < nb2) {
-        const int r = t / nb, a2 = t % nb;
-        double acc = 0.0;
-        for (int u = 0; u < nb; ++u) acc += H[r * nb + u] * V[u * m + a2];
-        Aug[t] = acc;
-    }
-    __syncthreads();
-    if (t < nb2) {
-        const int r = t / nb, c = t % nb;
-        double acc = 0.0;
-        for (int a2 = 0; a2 < nb; ++a2) {
-            const double ev = Lc[a2 * m + a2];
-            if (ev > PIVOT_TOL * emax) acc += Aug[r * nb + a2] * V[c * m + a2] / ev;
-        }
-        out[t] = acc;
-    }
-}
-
 // Normal equations of one block row: G = M M^T, H = E M^T, Lambda~ = H G^{-1}
 // (Cholesky; pseudo-inverse fallback).  A workgroup per list row, striding
 // over the nl rows; with only != null over the only[0] list rows only[1..].
@@ -908,8 +722,6 @@ __global__ __launch_bounds__(WG) void k_gram_solve(int nl, const int32_t *__rest
 // ... of the row; the four partial sums are added in LDS in wave order, then
 // the normal equations are solved as in k_gram_solve.  (For 8x8 blocks the
 // VALU kernel measured faster: half of every 16x16 product would be idle.)
-typedef double d4_t __attribute__((ext_vector_type(4)));
-
 __global__ __launch_bounds__(WG) void k_gram_mfma(const int32_t *__restrict__ list,
                                                   const int32_t *__restrict__ mptr, const int32_t *__restrict__ mcol,
                                                   const double *__restrict__ mval, const int32_t *__restrict__ eptr,
@@ -1640,7 +1452,8 @@ __global__ __launch_bounds__(WG) void k_eupdate(int B, int nb_rt, const int32_t 
                                                 const double *__restrict__ mval, const int32_t *__restrict__ eptr,
                                                 const int32_t *__restrict__ ecol, const double *__restrict__ eval,
                                                 const double *__restrict__ lamt, const int32_t *__restrict__ nptr,
-                                                int32_t *__restrict__ ncol, double *__restrict__ nval) {
+                                                int32_t *__restrict__ ncol, double *__restrict__ nval,
+                                                int copy_only) {
     constexpr int QCAP = NBT == 1 ? 256 : 4096;   // block positions of a row kept in LDS (point rows are short)
     __shared__ int32_t qpos[QCAP];
     const int i = blockIdx.x;
@@ -1650,6 +1463,7 @@ __global__ __launch_bounds__(WG) void k_eupdate(int B, int nb_rt, const int32_t 
     const int nb2 = nb * nb;
     const int li = pos_in_list[i];
     if (li == -2) return;   // member of a lattice class: translated from its representative
+    if (copy_only && li >= 0) return;   // the fused step has written it
     const int elo = eptr[i], ek = eptr[i + 1] - elo;
     const int nlo = nptr[i];
     if (li < 0) {   // unchanged row: copy (16-byte accesses, four in flight per thread)
@@ -1769,11 +1583,11 @@ __global__ __launch_bounds__(WG) void k_eupdate(int B, int nb_rt, const int32_t 
 
 void launch_eupdate(hipStream_t s, int B, int nb, const int32_t *pos, const int32_t *mptr, const int32_t *mcol,
                     const double *mval, const int32_t *eptr, const int32_t *ecol, const double *eval,
-                    const double *lamt, const int32_t *nptr, int32_t *ncol, double *nval) {
+                    const double *lamt, const int32_t *nptr, int32_t *ncol, double *nval, bool copy_only) {
     auto go = [&](auto nbc) {
         constexpr int NBT = decltype(nbc)::value;
         hipLaunchKernelGGL((k_eupdate<NBT>), dim3(B), dim3(WG), 0, s, B, nb, pos, mptr, mcol, mval, eptr, ecol, eval,
-                           lamt, nptr, ncol, nval);
+                           lamt, nptr, ncol, nval, copy_only ? 1 : 0);
     };
     switch (nb) {
         case 1: go(std::integral_constant<int, 1>{}); break;
@@ -2983,10 +2797,11 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
     keep_pattern(E.pat);
     DBuf<double> lamt((size_t)depth * B * nb2);
     CS_HIP(hipMemsetAsync(lamt.get(), 0, lamt.bytes(), s));   // rows of direct segments get no smoother
-    DBuf<int32_t> pos(B), sing, cnt, err(B), redo;
+    DBuf<int32_t> pos(B), sing, cnt, err(B), redo, rec8;
+    DBuf<uint16_t> pos8;
     DBuf<int64_t> tot(1);
     const int maxdeg = max_span(c, B, 1, ap.ptr.get());
-    int32_t emax = 1;   // longest block row of E (E_0 = I)
+    int32_t emax = 1, enext = 1;   // longest block row of E (E_0 = I), and of the updated one
     DBuf<int32_t> sing_acc(1);   // singular blocks of the fitted rows, read at the end
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(WG), 0, s, sing_acc.get(), (int64_t)1, 0);
     L.singular = 0;
@@ -3016,56 +2831,106 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
                                        E.pat.col.get(), cnt.get(), nullptr, nullptr, err.get());
             CS_LAUNCH_CHECK();
             int32_t overflow = 0;
-            mp.nnzb = scan_counts_ex(c, cnt, nl, mp.ptr, tot, nullptr, err.get(), nl, &overflow);
+            int32_t maxk = 0;   // longest row of M
+            mp.nnzb = scan_counts_ex(c, cnt, nl, mp.ptr, tot, nb == 8 ? &maxk : nullptr, err.get(), nl, &overflow);
             if (overflow) fail(CS_EINVAL, "fill of a residual row exceeds the per-row capacity of the symbolic kernels");
             mp.col.alloc(mp.nnzb);
             launch_union<SRC_E, true>(s, bound, dlist, nl, nb, ap.ptr.get(), ap.col.get(), E.pat.ptr.get(),
                                       E.pat.col.get(), nullptr, mp.ptr.get(), mp.col.get(), err.get());
             CS_LAUNCH_CHECK();
-            // numeric: M, normal equations, Lambda~
-            DBuf<double> mval((size_t)mp.nnzb * nb2);
-            if (nb == 1)
-                hipLaunchKernelGGL(k_rowprod_point, dim3((unsigned)ceil_div(nl, WG / 64)), dim3(WG), 0, s, nl,
-                                   dlist, ap.ptr.get(), ap.col.get(), abval.get(), E.pat.ptr.get(),
-                                   E.pat.col.get(), E.val.get(), mp.ptr.get(), mp.col.get(), mval.get());
-            else if (!rowprod_nb(s, nb, nl, dlist, ap, abval.get(), E, mp, mval.get(), maxdeg))
-                hipLaunchKernelGGL(k_rowprod, dim3(nl), dim3(WG), 0, s, dlist, nb, ap.ptr.get(), ap.col.get(),
-                                   abval.get(), E.pat.ptr.get(), E.pat.col.get(), E.val.get(), mp.ptr.get(),
-                                   mp.col.get(), mval.get());
-            CS_LAUNCH_CHECK();
             sing.alloc(nl);
             double *lam_l = lamt.get() + (size_t)(ell - 1) * B * nb2;
-            if (nb == 1)
-                hipLaunchKernelGGL(k_gram_point, dim3((unsigned)ceil_div(nl, WG / 64)), dim3(WG), 0, s, nl,
-                                   dlist, mp.ptr.get(), mp.col.get(), mval.get(), E.pat.ptr.get(),
-                                   E.pat.col.get(), E.val.get(), lam_l, sing.get(), o.ridge);
-            else {
-                auto go = [&](auto nbc) {
-                    constexpr int NBT = decltype(nbc)::value;
-                    hipLaunchKernelGGL((k_gram_solve<NBT>), dim3(nl), dim3(WG), 0, s, nl, dlist, nb, mp.ptr.get(),
-                                       mp.col.get(), mval.get(), E.pat.ptr.get(), E.pat.col.get(), E.val.get(),
-                                       lam_l, sing.get(), o.ridge, (const int32_t *)nullptr);
-                };
-                switch (nb) {
-                    case 2: go(std::integral_constant<int, 2>{}); break;
-                    case 4: go(std::integral_constant<int, 4>{}); break;
-                    case 8:
-                        // matrix cores, then the rows they flag through the minimum-norm path
-                        if (redo.n < (size_t)nl + 1) redo.alloc((size_t)nl + 1);   // grow only: a free syncs
-                        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(WG), 0, s, redo.get(), (int64_t)1, 0);
-                        hipLaunchKernelGGL(k_gram_mfma8, dim3((unsigned)ceil_div(nl, 8)), dim3(WG), 0, s, nl, dlist,
-                                           mp.ptr.get(), mp.col.get(), mval.get(), E.pat.ptr.get(),
-                                           E.pat.col.get(), E.val.get(), lam_l, sing.get(), redo.get(), o.ridge);
-                        hipLaunchKernelGGL((k_gram_solve<8>), dim3(256), dim3(WG), 0, s, nl, dlist, nb, mp.ptr.get(),
+            const bool more = step + 1 < nsteps;   // the last residual is never needed
+            // the updated E: pattern(M) for list rows, the old pattern for the others
+            EMat N;
+            auto new_pattern = [&]() {
+                DBuf<int32_t> ncnt(B);
+                hipLaunchKernelGGL(k_ecount, dim3(grid_for(B)), dim3(WG), 0, s, B, pos.get(), lrep, mp.ptr.get(),
+                                   E.pat.ptr.get(), ncnt.get());
+                CS_LAUNCH_CHECK();
+                N.pat.rows = B;
+                N.pat.nnzb = scan_counts_ex(c, ncnt, B, N.pat.ptr, tot, &enext, nullptr, 0, nullptr);
+                N.pat.col.alloc(N.pat.nnzb);
+                N.val.alloc((size_t)N.pat.nnzb * nb2);
+            };
+            // every block in the list, in order: the new pattern is M's
+            const bool all = o.mode == CS_ADDITIVE && !lattice && nl == B;
+            // 8x8 blocks whose rows of M fit in LDS: product, normal equations and
+            // update in one kernel, M never stored
+            Fit8 f8;
+            if (nb == 8) {
+                f8.nl = nl, f8.list = dlist;
+                f8.abptr = ap.ptr.get(), f8.abcol = ap.col.get(), f8.abval = abval.get();
+                f8.eptr = E.pat.ptr.get(), f8.ecol = E.pat.col.get(), f8.eval = E.val.get();
+                f8.mptr = mp.ptr.get(), f8.mcol = mp.col.get();
+                f8.lamt = lam_l, f8.sing = sing.get(), f8.ridge = o.ridge;
+                f8.identity = step == 0;
+                f8.maxk = maxk, f8.maxdeg = maxdeg;
+                f8.pcap = (int)std::min<int64_t>((int64_t)maxdeg * emax, INT32_MAX);
+                if (redo.n < (size_t)nl + 1) redo.alloc((size_t)nl + 1);   // grow only: a free syncs
+                f8.redo = redo.get();
+                hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(WG), 0, s, redo.get(), (int64_t)1, 0);
+                CS_LAUNCH_CHECK();
+            }
+            const bool fused = nb == 8 && fit8_fits(f8);
+            DBuf<double> mval;
+            if (fused) {
+                const size_t nrec = fit8_rec_ints(f8), npos = (size_t)nl * f8.pcap;
+                if (rec8.n < nrec) rec8.alloc(nrec);
+                if (pos8.n < npos) pos8.alloc(npos);
+                f8.rec = rec8.get(), f8.pos = pos8.get();
+                if (more && all) {
+                    N.val.alloc((size_t)mp.nnzb * nb2);
+                    f8.nptr = mp.ptr.get(), f8.nval = N.val.get();
+                    enext = maxk;
+                } else if (more) {
+                    new_pattern();
+                    f8.nptr = N.pat.ptr.get(), f8.ncol = N.pat.col.get(), f8.nval = N.val.get();
+                }
+                launch_fit8(s, f8);
+                if (more && all) N.pat = std::move(mp);
+            } else {
+                // numeric: M, normal equations, Lambda~
+                mval.alloc((size_t)mp.nnzb * nb2);
+                if (nb == 1)
+                    hipLaunchKernelGGL(k_rowprod_point, dim3((unsigned)ceil_div(nl, WG / 64)), dim3(WG), 0, s, nl,
+                                       dlist, ap.ptr.get(), ap.col.get(), abval.get(), E.pat.ptr.get(),
+                                       E.pat.col.get(), E.val.get(), mp.ptr.get(), mp.col.get(), mval.get());
+                else if (!rowprod_nb(s, nb, nl, dlist, ap, abval.get(), E, mp, mval.get(), maxdeg))
+                    hipLaunchKernelGGL(k_rowprod, dim3(nl), dim3(WG), 0, s, dlist, nb, ap.ptr.get(), ap.col.get(),
+                                       abval.get(), E.pat.ptr.get(), E.pat.col.get(), E.val.get(), mp.ptr.get(),
+                                       mp.col.get(), mval.get());
+                CS_LAUNCH_CHECK();
+                if (nb == 1)
+                    hipLaunchKernelGGL(k_gram_point, dim3((unsigned)ceil_div(nl, WG / 64)), dim3(WG), 0, s, nl,
+                                       dlist, mp.ptr.get(), mp.col.get(), mval.get(), E.pat.ptr.get(),
+                                       E.pat.col.get(), E.val.get(), lam_l, sing.get(), o.ridge);
+                else {
+                    auto go = [&](auto nbc) {
+                        constexpr int NBT = decltype(nbc)::value;
+                        hipLaunchKernelGGL((k_gram_solve<NBT>), dim3(nl), dim3(WG), 0, s, nl, dlist, nb, mp.ptr.get(),
                                            mp.col.get(), mval.get(), E.pat.ptr.get(), E.pat.col.get(), E.val.get(),
-                                           lam_l, sing.get(), o.ridge, (const int32_t *)redo.get());
-                        break;
-                    case 16:
-                        hipLaunchKernelGGL(k_gram_mfma, dim3(nl), dim3(WG), 0, s, dlist, mp.ptr.get(),
-                                           mp.col.get(), mval.get(), E.pat.ptr.get(), E.pat.col.get(),
-                                           E.val.get(), lam_l, sing.get(), o.ridge);
-                        break;
-                    default: go(std::integral_constant<int, 0>{}); break;
+                                           lam_l, sing.get(), o.ridge, (const int32_t *)nullptr);
+                    };
+                    switch (nb) {
+                        case 2: go(std::integral_constant<int, 2>{}); break;
+                        case 4: go(std::integral_constant<int, 4>{}); break;
+                        case 8:
+                            // matrix cores, then the rows they flag through the minimum-norm path
+                            hipLaunchKernelGGL(k_gram_mfma8, dim3((unsigned)ceil_div(nl, 8)), dim3(WG), 0, s, nl, dlist,
+                                               mp.ptr.get(), mp.col.get(), mval.get(), E.pat.ptr.get(),
+                                               E.pat.col.get(), E.val.get(), lam_l, sing.get(), redo.get(), o.ridge);
+                            hipLaunchKernelGGL((k_gram_solve<8>), dim3(256), dim3(WG), 0, s, nl, dlist, nb, mp.ptr.get(),
+                                               mp.col.get(), mval.get(), E.pat.ptr.get(), E.pat.col.get(), E.val.get(),
+                                               lam_l, sing.get(), o.ridge, (const int32_t *)redo.get());
+                            break;
+                        case 16:
+                            hipLaunchKernelGGL(k_gram_mfma, dim3(nl), dim3(WG), 0, s, dlist, mp.ptr.get(),
+                                               mp.col.get(), mval.get(), E.pat.ptr.get(), E.pat.col.get(),
+                                               E.val.get(), lam_l, sing.get(), o.ridge);
+                            break;
+                        default: go(std::integral_constant<int, 0>{}); break;
+                    }
                 }
             }
             hipLaunchKernelGGL(k_reduce_i32<true>, dim3(std::min<unsigned>(grid_for(nl), 4096)), dim3(WG), 0, s,
@@ -3078,21 +2943,17 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
                                    (int64_t)B, msing.get(), lat_acc.get());
                 CS_LAUNCH_CHECK();
             }
-            if (step + 1 == nsteps) break;   // the last residual is never needed
-            // E update on pattern(M) for list rows, copy for others
+            if (!more) break;
             {
-                DBuf<int32_t> ncnt(B);
-                hipLaunchKernelGGL(k_ecount, dim3(grid_for(B)), dim3(WG), 0, s, B, pos.get(), lrep, mp.ptr.get(),
-                                   E.pat.ptr.get(), ncnt.get());
+                // the fused step leaves the rows off the list to copy (direct
+                // segments, the other colours)
+                if (!fused) new_pattern();
+                if (!fused || !all)
+                    launch_eupdate(s, B, nb, pos.get(), mp.ptr.get(), mp.col.get(), mval.get(), E.pat.ptr.get(),
+                                   E.pat.col.get(), E.val.get(), lam_l, N.pat.ptr.get(), N.pat.col.get(), N.val.get(),
+                                   fused);
                 CS_LAUNCH_CHECK();
-                EMat N;
-                N.pat.rows = B;
-                N.pat.nnzb = scan_counts_ex(c, ncnt, B, N.pat.ptr, tot, &emax, nullptr, 0, nullptr);
-                N.pat.col.alloc(N.pat.nnzb);
-                N.val.alloc((size_t)N.pat.nnzb * nb2);
-                launch_eupdate(s, B, nb, pos.get(), mp.ptr.get(), mp.col.get(), mval.get(), E.pat.ptr.get(),
-                               E.pat.col.get(), E.val.get(), lam_l, N.pat.ptr.get(), N.pat.col.get(), N.val.get());
-                CS_LAUNCH_CHECK();
+                emax = enext;
                 if (lrep) {
                     // rows read by step ell + 1: its list (the classes at radius ell) and their neighbours
                     hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(B)), dim3(WG), 0, s, need.get(), (int64_t)B, 0);

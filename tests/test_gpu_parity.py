@@ -151,6 +151,37 @@ def test_deep_cascade_long_rows(gpu_lib):
     s.close()
 
 
+@pytest.mark.parametrize("n,depth,mode,alpha", [
+    (8, 4, "additive", None),            # every row reaches every other; 27 blocks on the coarse level
+    (12, 5, "additive", None),           # rows of up to 216 blocks: the last step leaves the fused kernel
+    (12, 4, "additive", 9),              # truncated rows between fused steps
+    (12, 2, "multiplicative", None),     # rows off the colour are copied
+])
+def test_fused_fit_of_8x8_blocks(gpu_lib, n, depth, mode, alpha):
+    """The fit of 8x8 blocks with a row of M in LDS, on random coefficients."""
+    mu = np.exp(stream(61, TEST, n).standard_normal((n, n, n)))
+    levels = fd.fv_hierarchy(mu, bs=2, n_stop=3)
+    p = Problem(f"lognormal3d_{n}", levels, np.zeros((n ** 3, 1)))
+    sm = oracle_setup(p, depth, mode, alpha)
+    s = gpu_solver(gpu_lib, p, depth=depth, mode=mode, order="FF", alpha=alpha or 0)
+    check_smoothers(s, sm, p, depth, f"{p.name} {mode} depth {depth} alpha {alpha}")
+    check_patterns(s, sm, p)
+    s.close()
+
+
+def test_fused_fit_27_point_rows(gpu_lib):
+    """27 neighbours per row: rows of 27, 125 and 216 blocks, the last beyond the
+    fused kernel."""
+    from synth import fe
+    levels = fe.galerkin_hierarchy(fe.assemble(np.exp(stream(61, TEST, 3).standard_normal((12, 12, 12)))), 12)
+    p = Problem("q1_lognormal_12", levels, np.zeros((12 ** 3, 1)))
+    sm = oracle_setup(p, 3)
+    s = gpu_solver(gpu_lib, p, depth=3)
+    check_smoothers(s, sm, p, 3)
+    check_patterns(s, sm, p)
+    s.close()
+
+
 @pytest.mark.parametrize("order", ["RF", "FF"])
 def test_interface_vcycle_fp64_and_fp32(gpu_lib, iface32, order):
     p, sm = iface32
