@@ -43,6 +43,15 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t bid, int64_t G) {
 void *pool_alloc(size_t bytes);   // throws CS_ENOMEM
 void pool_free(void *p);
 void pool_user(int delta);        // contexts alive; the cache is emptied when none are
+// While it lives, this thread's frees wait for the device once, at its end, and
+// blocks allocated meanwhile are reused in stream order: for work on one stream.
+struct PoolScope {
+    PoolScope();
+    ~PoolScope();
+    PoolScope(const PoolScope &) = delete;
+    PoolScope &operator=(const PoolScope &) = delete;
+    void *state = nullptr;
+};
 
 // Owning device buffer.
 template <class T>
@@ -263,6 +272,7 @@ struct Ctx {
     DBuf<double> cg_partial;            // batch: flat-kernel partial sums [workgroups][R]
     double *h_norm = nullptr;           // pinned host copy of ir_norm
     size_t h_norm_cap = 0;
+    int64_t *h_rb = nullptr;            // pinned; the setup's kernels write sizes and flags there
     // GMRES: unnormalised basis [m+1][n][R], preconditioned vectors (flexible)
     // [m][n][R], two work vectors, reciprocal basis norms [m+1][nsys][R],
     // Hessenberg columns of two Gram-Schmidt passes and the new norm, the

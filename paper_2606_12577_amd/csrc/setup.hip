@@ -197,7 +197,10 @@ __global__ __launch_bounds__(WG) void k_union(const int32_t *__restrict__ list, 
     }
     __syncthreads();
     if (!FILL) {
-        if (t == 0) out_cnt[li] = part[WG];
+        if (t == 0) {
+            out_cnt[li] = part[WG];
+            err[li] = 0;
+        }
     } else {
         int o = out_ptr[li] + part[t];
         for (int a = a0; a < a1; ++a) {
@@ -327,7 +330,10 @@ __global__ __launch_bounds__(WG) void k_union_wave(const int32_t *__restrict__ l
         }
         count += __popcll(mask);
     }
-    if (!FILL && live && lane == 0) out_cnt[li] = count;
+    if (!FILL && live && lane == 0) {
+        out_cnt[li] = count;
+        err[li] = 0;
+    }
 }
 
 // Exclusive prefix sum of n counts in three passes: every workgroup scans 1024
@@ -387,11 +393,106 @@ __global__ __launch_bounds__(256) void k_scan_sums(int64_t ntiles, int64_t *__re
     if (threadIdx.x == 0) total_out[0] = carry;
 }
 
+// host (pinned): {total, maxima[0], maxima[1]} for the host to read
 __global__ __launch_bounds__(256) void k_scan_add(int64_t n, const int64_t *__restrict__ tile_off,
-                                                  const int64_t *__restrict__ total, int32_t *__restrict__ ptr) {
+                                                  const int64_t *__restrict__ total, int32_t *__restrict__ ptr,
+                                                  const int32_t *__restrict__ maxima, int64_t *__restrict__ host) {
     const int64_t a = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (a < n) ptr[a] += (int32_t)tile_off[a / SCAN_TILE];
-    if (a == 0) ptr[n] = (int32_t)total[0];
+    if (a == 0) {
+        ptr[n] = (int32_t)total[0];
+        host[0] = total[0];
+        host[1] = maxima[0];
+        host[2] = maxima[1];
+    }
+}
+
+// The same for at most SCAN_SMALL counts and flags in one launch: a workgroup
+// scans, eight counts per thread, and finds both maxima.  (The setup of the 64^2
+// SIPG problem scans 96 times, at most 4,096 counts each; six launches and two
+// copies every time before.)
+constexpr int64_t SCAN_SMALL = 8192;
+__global__ __launch_bounds__(1024) void k_scan_small(const int32_t *__restrict__ cnt, int n, int32_t *__restrict__ ptr,
+                                                     const int32_t *__restrict__ flags, int nflags,
+                                                     int64_t *__restrict__ host) {
+    __shared__ int64_t wsum[16];
+    __shared__ int32_t wmax[2][16];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    int32_t v[8], mx = 0, fl = 0;
+    int64_t local = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const int e = t * 8 + u;
+        v[u] = e < n ? cnt[e] : 0;
+        local += v[u];
+        mx = max(mx, v[u]);
+    }
+    for (int e = t; e < nflags; e += 1024) fl = max(fl, flags[e]);
+    int64_t inc = local;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int64_t y = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += y;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        mx = max(mx, __shfl_xor(mx, o, 64));
+        fl = max(fl, __shfl_xor(fl, o, 64));
+    }
+    if (lane == 63) wsum[wave] = inc;
+    if (lane == 0) {
+        wmax[0][wave] = mx;
+        wmax[1][wave] = fl;
+    }
+    __syncthreads();
+    int64_t base = 0, total = 0;
+    for (int w = 0; w < 16; ++w) {
+        if (w < wave) base += wsum[w];
+        total += wsum[w];
+    }
+    int64_t o = base + inc - local;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const int e = t * 8 + u;
+        if (e < n) ptr[e] = (int32_t)o;
+        o += v[u];
+    }
+    if (t == 0) {
+        for (int w = 1; w < 16; ++w) {
+            mx = max(mx, wmax[0][w]);
+            fl = max(fl, wmax[1][w]);
+        }
+        ptr[n] = (int32_t)total;
+        host[0] = total;
+        host[1] = mx;
+        host[2] = fl;
+    }
+}
+
+// Sum or maximum (of a, or of the spans ptr[stride (i + 1)] - ptr[stride i]) of at
+// most REDUCE_SMALL values by one workgroup, into pinned host memory.
+constexpr int64_t REDUCE_SMALL = 32768;
+enum { RED_MAX = 0, RED_SUM = 1, RED_SPAN = 2 };
+template <int MODE>
+__global__ __launch_bounds__(1024) void k_reduce_small(int n, int stride, const int32_t *__restrict__ a,
+                                                       int64_t *__restrict__ host) {
+    __shared__ int32_t red[16];
+    int32_t v = 0;
+    for (int e = threadIdx.x; e < n; e += 1024) {
+        const int32_t x = MODE == RED_SPAN ? a[(int64_t)(e + 1) * stride] - a[(int64_t)e * stride] : a[e];
+        v = MODE == RED_SUM ? v + x : max(v, x);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const int32_t y = __shfl_xor(v, o, 64);
+        v = MODE == RED_SUM ? v + y : max(v, y);
+    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 16; ++w) v = MODE == RED_SUM ? v + red[w] : max(v, red[w]);
+        host[0] = v;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1691,6 +1792,14 @@ __global__ void k_pos_in_list(const int32_t *__restrict__ list, int nlist, int32
     if (t < nlist) pos[list[t]] = t;
 }
 
+// pos[i] = where[i] - first where that is in [0, n), else -1
+__global__ void k_pos_range(int B, const int32_t *__restrict__ where, int first, int n, int32_t *__restrict__ pos) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= B) return;
+    const int q = where[i] - first;
+    pos[i] = q >= 0 && q < n ? q : -1;
+}
+
 __global__ void k_iota(int32_t *a, int n) {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t < n) a[t] = t;
@@ -2299,57 +2408,65 @@ struct EMat {
     DBuf<double> val;
 };
 
-int64_t scan_counts(Ctx &c, const DBuf<int32_t> &cnt, int64_t n, DBuf<int32_t> &ptr, DBuf<int64_t> &tot) {
-    ptr.alloc(n + 1);
-    const int64_t ntiles = std::max<int64_t>(ceil_div(n, SCAN_TILE), 1);
-    DBuf<int64_t> tiles(ntiles);
-    hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)ntiles), dim3(256), 0, c.stream, cnt.get(), n, ptr.get(),
-                       tiles.get());
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(256), 0, c.stream, ntiles, tiles.get(), tot.get());
-    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)ceil_div(n + 1, 256)), dim3(256), 0, c.stream, n, tiles.get(),
-                       tot.get(), ptr.get());
-    CS_LAUNCH_CHECK();
-    int64_t total = 0;
-    tot.download(&total, 1, c.stream);
-    CS_HIP(hipStreamSynchronize(c.stream));
-    if (total >= INT32_MAX) fail(CS_ENOMEM, "pattern too large for 32-bit offsets");
-    return total;
+// the pinned read-back of the setup's kernels
+int64_t *readback(Ctx &c) {
+    if (!c.h_rb) CS_HIP(hipHostMalloc(reinterpret_cast<void **>(&c.h_rb), 4 * sizeof(int64_t)));
+    return c.h_rb;
 }
 
-// scan_counts that also brings back, in the same round trip, max(cnt[0, n))
-// (when maxc) and max(flags[0, nflags)) (when flags)
-int64_t scan_counts_ex(Ctx &c, const DBuf<int32_t> &cnt, int64_t n, DBuf<int32_t> &ptr, DBuf<int64_t> &tot,
-                       int32_t *maxc, const int32_t *flags, int64_t nflags, int32_t *flag) {
-    DBuf<int32_t> m(2);
+// Exclusive prefix sum of n counts into ptr[0, n]; returns the total and, in the
+// same round trip, max(cnt[0, n)) (when maxc) and max(flags[0, nflags)) (when flag).
+int64_t scan_counts_ex(Ctx &c, const DBuf<int32_t> &cnt, int64_t n, DBuf<int32_t> &ptr, int32_t *maxc,
+                       const int32_t *flags, int64_t nflags, int32_t *flag) {
     hipStream_t s = c.stream;
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(WG), 0, s, m.get(), (int64_t)2, 0);
-    if (maxc && n > 0)
-        hipLaunchKernelGGL(k_reduce_i32<false>, dim3((unsigned)std::min<int64_t>(ceil_div(n, WG), 4096)), dim3(WG), 0,
-                           s, n, cnt.get(), m.get());
-    if (flags && nflags > 0)
-        hipLaunchKernelGGL(k_reduce_i32<false>, dim3((unsigned)std::min<int64_t>(ceil_div(nflags, WG), 4096)),
-                           dim3(WG), 0, s, nflags, flags, m.get() + 1);
+    int64_t *host = readback(c);
     ptr.alloc(n + 1);
-    const int64_t ntiles = std::max<int64_t>(ceil_div(n, SCAN_TILE), 1);
-    DBuf<int64_t> tiles(ntiles);
-    hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)ntiles), dim3(256), 0, s, cnt.get(), n, ptr.get(), tiles.get());
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(256), 0, s, ntiles, tiles.get(), tot.get());
-    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)ceil_div(n + 1, 256)), dim3(256), 0, s, n, tiles.get(), tot.get(),
-                       ptr.get());
-    CS_LAUNCH_CHECK();
-    int64_t total = 0;
-    int32_t hm[2] = {0, 0};
-    tot.download(&total, 1, s);
-    m.download(hm, 2, s);
-    CS_HIP(hipStreamSynchronize(s));
-    if (maxc) *maxc = hm[0];
-    if (flag) *flag = hm[1];
-    if (total >= INT32_MAX) fail(CS_ENOMEM, "pattern too large for 32-bit offsets");
-    return total;
+    if (!flags) nflags = 0;
+    if (n <= SCAN_SMALL && nflags <= 4 * SCAN_SMALL) {
+        hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, cnt.get(), (int)n, ptr.get(), flags, (int)nflags,
+                           host);
+        CS_LAUNCH_CHECK();
+        CS_HIP(hipStreamSynchronize(s));
+    } else {
+        DBuf<int32_t> m(2);
+        DBuf<int64_t> tot(1);
+        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(WG), 0, s, m.get(), (int64_t)2, 0);
+        if (maxc && n > 0)
+            hipLaunchKernelGGL(k_reduce_i32<false>, dim3((unsigned)std::min<int64_t>(ceil_div(n, WG), 4096)), dim3(WG),
+                               0, s, n, cnt.get(), m.get());
+        if (nflags > 0)
+            hipLaunchKernelGGL(k_reduce_i32<false>, dim3((unsigned)std::min<int64_t>(ceil_div(nflags, WG), 4096)),
+                               dim3(WG), 0, s, nflags, flags, m.get() + 1);
+        const int64_t ntiles = std::max<int64_t>(ceil_div(n, SCAN_TILE), 1);
+        DBuf<int64_t> tiles(ntiles);
+        hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)ntiles), dim3(256), 0, s, cnt.get(), n, ptr.get(),
+                           tiles.get());
+        hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(256), 0, s, ntiles, tiles.get(), tot.get());
+        hipLaunchKernelGGL(k_scan_add, dim3((unsigned)ceil_div(n + 1, 256)), dim3(256), 0, s, n, tiles.get(),
+                           tot.get(), ptr.get(), m.get(), host);
+        CS_LAUNCH_CHECK();
+        CS_HIP(hipStreamSynchronize(s));
+    }
+    if (maxc) *maxc = (int32_t)host[1];
+    if (flag) *flag = (int32_t)host[2];
+    if (host[0] >= INT32_MAX) fail(CS_ENOMEM, "pattern too large for 32-bit offsets");
+    return host[0];
+}
+
+int64_t scan_counts(Ctx &c, const DBuf<int32_t> &cnt, int64_t n, DBuf<int32_t> &ptr) {
+    return scan_counts_ex(c, cnt, n, ptr, nullptr, nullptr, 0, nullptr);
 }
 
 // sum (or max) of n device ints, on the host
 int32_t reduce_i32(Ctx &c, const int32_t *a, int64_t n, bool sum) {
+    if (n <= REDUCE_SMALL) {
+        int64_t *host = readback(c);
+        if (sum) hipLaunchKernelGGL(k_reduce_small<RED_SUM>, dim3(1), dim3(1024), 0, c.stream, (int)n, 1, a, host);
+        else hipLaunchKernelGGL(k_reduce_small<RED_MAX>, dim3(1), dim3(1024), 0, c.stream, (int)n, 1, a, host);
+        CS_LAUNCH_CHECK();
+        CS_HIP(hipStreamSynchronize(c.stream));
+        return (int32_t)host[0];
+    }
     DBuf<int32_t> m(1);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(WG), 0, c.stream, m.get(), (int64_t)1, 0);
     const unsigned g = (unsigned)std::min<int64_t>(std::max<int64_t>(ceil_div(n, WG), 1), 4096);
@@ -2502,6 +2619,13 @@ void build_colour_layout(Ctx &c, Level &L) {
 namespace {
 
 int max_span(Ctx &c, int64_t n, int stride, const int32_t *ptr) {
+    if (n <= REDUCE_SMALL) {
+        int64_t *host = readback(c);
+        hipLaunchKernelGGL(k_reduce_small<RED_SPAN>, dim3(1), dim3(1024), 0, c.stream, (int)n, stride, ptr, host);
+        CS_LAUNCH_CHECK();
+        CS_HIP(hipStreamSynchronize(c.stream));
+        return (int)host[0];
+    }
     DBuf<int32_t> m(1);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(WG), 0, c.stream, m.get(), (int64_t)1, 0);
     hipLaunchKernelGGL(k_max_span, dim3(grid_for(std::max<int64_t>(n, 1))), dim3(WG), 0, c.stream, n, stride, ptr,
@@ -2544,15 +2668,13 @@ void launch_union(hipStream_t s, int64_t bound, const int32_t *list, int nl, int
 void block_pattern_of_A(Ctx &c, Level &L, BPattern &ap) {
     const int B = (int)L.B;
     DBuf<int32_t> cnt(B), err(B);
-    DBuf<int64_t> tot(1);
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(B)), dim3(WG), 0, c.stream, err.get(), (int64_t)B, 0);
     const int64_t bound = max_span(c, B, (int)L.nb, L.a_ptr.get());
     launch_union<SRC_SCALAR, false>(c.stream, bound, nullptr, B, (int)L.nb, L.a_ptr.get(), L.a_col.get(), nullptr,
                                     nullptr, cnt.get(), nullptr, nullptr, err.get());
     CS_LAUNCH_CHECK();
     check_flags(c, err, B, "block row of A");
     ap.rows = B;
-    ap.nnzb = scan_counts(c, cnt, B, ap.ptr, tot);
+    ap.nnzb = scan_counts(c, cnt, B, ap.ptr);
     ap.col.alloc(ap.nnzb);
     launch_union<SRC_SCALAR, true>(c.stream, bound, nullptr, B, (int)L.nb, L.a_ptr.get(), L.a_col.get(), nullptr,
                                    nullptr, nullptr, ap.ptr.get(), ap.col.get(), err.get());
@@ -2701,7 +2823,6 @@ void lattice_classes(Ctx &c, Level &L, const BPattern &ap, int depth, std::vecto
     while (T < 2 * (int64_t)std::max(Ba, 1) + 1) T <<= 1;
     DBuf<uint64_t> tk(T), key(std::max(Ba, 1));
     DBuf<int32_t> tm(T), flag(std::max(Ba, 1)), off;
-    DBuf<int64_t> tot(1);
     L.lat_rep.alloc((size_t)depth * B);
     lists.clear();
     lists.resize(depth);
@@ -2729,7 +2850,7 @@ void lattice_classes(Ctx &c, Level &L, const BPattern &ap, int depth, std::vecto
                                prev, key.get(), T, tk.get(), tm.get(), rep);
         hipLaunchKernelGGL(k_lat_flag, dim3(grid_for(Ba)), dim3(WG), 0, s, Ba, rep, flag.get());
         CS_LAUNCH_CHECK();
-        sizes[r] = (int)scan_counts(c, flag, Ba, off, tot);
+        sizes[r] = (int)scan_counts(c, flag, Ba, off);
         lists[r].alloc(std::max(sizes[r], 1));
         hipLaunchKernelGGL(k_lat_compact, dim3(grid_for(Ba)), dim3(WG), 0, s, Ba, rep, off.get(), lists[r].get());
         CS_LAUNCH_CHECK();
@@ -2783,27 +2904,26 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
     hipLaunchKernelGGL(k_identity_E, dim3(grid_for((int64_t)B * nb2)), dim3(WG), 0, s, B, nb, E.pat.ptr.get(),
                        E.pat.col.get(), E.val.get());
     CS_LAUNCH_CHECK();
-    auto keep_pattern = [&](const BPattern &p) {
-        BPattern q;
-        q.rows = p.rows;
-        q.nnzb = p.nnzb;
-        q.ptr.alloc(p.rows + 1);
-        q.col.alloc(std::max<int64_t>(p.nnzb, 1));
-        CS_HIP(hipMemcpyAsync(q.ptr.get(), p.ptr.get(), (p.rows + 1) * 4, hipMemcpyDeviceToDevice, s));
-        if (p.nnzb) CS_HIP(hipMemcpyAsync(q.col.get(), p.col.get(), p.nnzb * 4, hipMemcpyDeviceToDevice, s));
-        L.patterns.push_back(std::move(q));
-    };
-    L.patterns.clear();
-    keep_pattern(E.pat);
+    L.patterns.clear();   // E's patterns move there as E is replaced
     DBuf<double> lamt((size_t)depth * B * nb2);
     CS_HIP(hipMemsetAsync(lamt.get(), 0, lamt.bytes(), s));   // rows of direct segments get no smoother
-    DBuf<int32_t> pos(B), sing, cnt, err(B), redo, rec8;
+    DBuf<int32_t> pos(B), cnt, err(B), redo, rec8;
     DBuf<uint16_t> pos8;
-    DBuf<int64_t> tot(1);
     const int maxdeg = max_span(c, B, 1, ap.ptr.get());
     int32_t emax = 1, enext = 1;   // longest block row of E (E_0 = I), and of the updated one
-    DBuf<int32_t> sing_acc(1);   // singular blocks of the fitted rows, read at the end
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(WG), 0, s, sing_acc.get(), (int64_t)1, 0);
+    DBuf<int32_t> sing_all((size_t)depth * B);   // singular flags of all steps' rows, counted at the end
+    int64_t nsing = 0;
+    // position of every block in the lists (one after the other), -1: none
+    DBuf<int32_t> where;
+    if (!lattice) {
+        where.alloc(B);
+        hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(B)), dim3(WG), 0, s, where.get(), (int64_t)B, -1);
+        int off = 0;
+        for (const auto &l : lists) off += l.second;
+        if (off > 0)   // (the lists lie one after the other)
+            hipLaunchKernelGGL(k_pos_in_list, dim3(grid_for(off)), dim3(WG), 0, s, lists[0].first, off, where.get());
+        CS_LAUNCH_CHECK();
+    }
     L.singular = 0;
     const int nsteps = depth * (int)lists.size();
     int step = 0;
@@ -2818,10 +2938,14 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
                 lrep = L.lat_rep.get() + (size_t)(ell - 1) * B;
             }
             if (nl == 0) continue;
-            hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(B)), dim3(WG), 0, s, pos.get(), (int64_t)B, -1);
-            hipLaunchKernelGGL(k_pos_in_list, dim3(grid_for(nl)), dim3(WG), 0, s, dlist, nl, pos.get());
-            if (lrep) hipLaunchKernelGGL(k_lat_mark, dim3(grid_for(B)), dim3(WG), 0, s, B, lrep, pos.get());
-            hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(B)), dim3(WG), 0, s, err.get(), (int64_t)B, 0);
+            if (lattice) {
+                hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(B)), dim3(WG), 0, s, pos.get(), (int64_t)B, -1);
+                hipLaunchKernelGGL(k_pos_in_list, dim3(grid_for(nl)), dim3(WG), 0, s, dlist, nl, pos.get());
+                hipLaunchKernelGGL(k_lat_mark, dim3(grid_for(B)), dim3(WG), 0, s, B, lrep, pos.get());
+            } else if (step == 0 || lists.size() > 1) {
+                hipLaunchKernelGGL(k_pos_range, dim3(grid_for(B)), dim3(WG), 0, s, B, where.get(),
+                                   (int)(dlist - lists[0].first), nl, pos.get());
+            }
             // symbolic: pattern(M_i) for the list rows
             cnt.alloc(nl);
             BPattern mp;
@@ -2832,13 +2956,14 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
             CS_LAUNCH_CHECK();
             int32_t overflow = 0;
             int32_t maxk = 0;   // longest row of M
-            mp.nnzb = scan_counts_ex(c, cnt, nl, mp.ptr, tot, nb == 8 ? &maxk : nullptr, err.get(), nl, &overflow);
+            mp.nnzb = scan_counts_ex(c, cnt, nl, mp.ptr, nb == 8 ? &maxk : nullptr, err.get(), nl, &overflow);
             if (overflow) fail(CS_EINVAL, "fill of a residual row exceeds the per-row capacity of the symbolic kernels");
             mp.col.alloc(mp.nnzb);
             launch_union<SRC_E, true>(s, bound, dlist, nl, nb, ap.ptr.get(), ap.col.get(), E.pat.ptr.get(),
                                       E.pat.col.get(), nullptr, mp.ptr.get(), mp.col.get(), err.get());
             CS_LAUNCH_CHECK();
-            sing.alloc(nl);
+            int32_t *const sing = sing_all.get() + nsing;
+            nsing += nl;
             double *lam_l = lamt.get() + (size_t)(ell - 1) * B * nb2;
             const bool more = step + 1 < nsteps;   // the last residual is never needed
             // the updated E: pattern(M) for list rows, the old pattern for the others
@@ -2849,7 +2974,7 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
                                    E.pat.ptr.get(), ncnt.get());
                 CS_LAUNCH_CHECK();
                 N.pat.rows = B;
-                N.pat.nnzb = scan_counts_ex(c, ncnt, B, N.pat.ptr, tot, &enext, nullptr, 0, nullptr);
+                N.pat.nnzb = scan_counts_ex(c, ncnt, B, N.pat.ptr, &enext, nullptr, 0, nullptr);
                 N.pat.col.alloc(N.pat.nnzb);
                 N.val.alloc((size_t)N.pat.nnzb * nb2);
             };
@@ -2863,7 +2988,7 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
                 f8.abptr = ap.ptr.get(), f8.abcol = ap.col.get(), f8.abval = abval.get();
                 f8.eptr = E.pat.ptr.get(), f8.ecol = E.pat.col.get(), f8.eval = E.val.get();
                 f8.mptr = mp.ptr.get(), f8.mcol = mp.col.get();
-                f8.lamt = lam_l, f8.sing = sing.get(), f8.ridge = o.ridge;
+                f8.lamt = lam_l, f8.sing = sing, f8.ridge = o.ridge;
                 f8.identity = step == 0;
                 f8.maxk = maxk, f8.maxdeg = maxdeg;
                 f8.pcap = (int)std::min<int64_t>((int64_t)maxdeg * emax, INT32_MAX);
@@ -2904,13 +3029,13 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
                 if (nb == 1)
                     hipLaunchKernelGGL(k_gram_point, dim3((unsigned)ceil_div(nl, WG / 64)), dim3(WG), 0, s, nl,
                                        dlist, mp.ptr.get(), mp.col.get(), mval.get(), E.pat.ptr.get(),
-                                       E.pat.col.get(), E.val.get(), lam_l, sing.get(), o.ridge);
+                                       E.pat.col.get(), E.val.get(), lam_l, sing, o.ridge);
                 else {
                     auto go = [&](auto nbc) {
                         constexpr int NBT = decltype(nbc)::value;
                         hipLaunchKernelGGL((k_gram_solve<NBT>), dim3(nl), dim3(WG), 0, s, nl, dlist, nb, mp.ptr.get(),
                                            mp.col.get(), mval.get(), E.pat.ptr.get(), E.pat.col.get(), E.val.get(),
-                                           lam_l, sing.get(), o.ridge, (const int32_t *)nullptr);
+                                           lam_l, sing, o.ridge, (const int32_t *)nullptr);
                     };
                     switch (nb) {
                         case 2: go(std::integral_constant<int, 2>{}); break;
@@ -2919,26 +3044,23 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
                             // matrix cores, then the rows they flag through the minimum-norm path
                             hipLaunchKernelGGL(k_gram_mfma8, dim3((unsigned)ceil_div(nl, 8)), dim3(WG), 0, s, nl, dlist,
                                                mp.ptr.get(), mp.col.get(), mval.get(), E.pat.ptr.get(),
-                                               E.pat.col.get(), E.val.get(), lam_l, sing.get(), redo.get(), o.ridge);
+                                               E.pat.col.get(), E.val.get(), lam_l, sing, redo.get(), o.ridge);
                             hipLaunchKernelGGL((k_gram_solve<8>), dim3(256), dim3(WG), 0, s, nl, dlist, nb, mp.ptr.get(),
                                                mp.col.get(), mval.get(), E.pat.ptr.get(), E.pat.col.get(), E.val.get(),
-                                               lam_l, sing.get(), o.ridge, (const int32_t *)redo.get());
+                                               lam_l, sing, o.ridge, (const int32_t *)redo.get());
                             break;
                         case 16:
                             hipLaunchKernelGGL(k_gram_mfma, dim3(nl), dim3(WG), 0, s, dlist, mp.ptr.get(),
                                                mp.col.get(), mval.get(), E.pat.ptr.get(), E.pat.col.get(),
-                                               E.val.get(), lam_l, sing.get(), o.ridge);
+                                               E.val.get(), lam_l, sing, o.ridge);
                             break;
                         default: go(std::integral_constant<int, 0>{}); break;
                     }
                 }
             }
-            hipLaunchKernelGGL(k_reduce_i32<true>, dim3(std::min<unsigned>(grid_for(nl), 4096)), dim3(WG), 0, s,
-                               (int64_t)nl, sing.get(), sing_acc.get());
-            CS_LAUNCH_CHECK();
             if (lrep) {
                 hipLaunchKernelGGL(k_lat_copy_lam, dim3(grid_for((int64_t)B * nb2)), dim3(WG), 0, s, B, nb2, lrep,
-                                   pos.get(), sing.get(), lam_l, msing.get());
+                                   pos.get(), sing, lam_l, msing.get());
                 hipLaunchKernelGGL(k_reduce_i32<true>, dim3(std::min<unsigned>(grid_for(B), 4096)), dim3(WG), 0, s,
                                    (int64_t)B, msing.get(), lat_acc.get());
                 CS_LAUNCH_CHECK();
@@ -2977,7 +3099,7 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
                     int32_t tover = 0;
                     EMat T;
                     T.pat.rows = B;
-                    T.pat.nnzb = scan_counts_ex(c, tcnt, B, T.pat.ptr, tot, &emax, err.get(), B, &tover);
+                    T.pat.nnzb = scan_counts_ex(c, tcnt, B, T.pat.ptr, &emax, err.get(), B, &tover);
                     if (tover)
                         fail(CS_EINVAL, "truncated residual row exceeds the per-row capacity of the symbolic kernels");
                     T.pat.col.alloc(T.pat.nnzb);
@@ -2988,16 +3110,17 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
                     CS_LAUNCH_CHECK();
                     N = std::move(T);
                 }
+                L.patterns.push_back(std::move(E.pat));
                 E = std::move(N);
-                keep_pattern(E.pat);
             }
         }
     }
+    L.patterns.push_back(std::move(E.pat));
     {
-        int32_t acc[2] = {0, 0}, sg = 0;
-        sing_acc.download(&sg, 1, s);
+        int32_t acc[2] = {0, 0};
         if (lattice) lat_acc.download(acc, 2, s);
-        CS_HIP(hipStreamSynchronize(s));
+        const int32_t sg = nsing > 0 ? reduce_i32(c, sing_all.get(), nsing, true) : 0;   // waits for the stream
+        if (lattice) CS_HIP(hipStreamSynchronize(s));
         if (acc[1])
             fail(CS_EINVAL, "a residual row of a lattice class could not be translated (row above " +
                                 std::to_string(LAT_ROW_CAP) + " blocks, or a neighbour off the lattice)");
@@ -3047,7 +3170,6 @@ void fit_level_overlap_exact(Ctx &c, Level &L, const cs_options &o) {
                        E.val.get());
     CS_LAUNCH_CHECK();
     DBuf<int32_t> list(n), cnt(n), err(n), sing(nblk);
-    DBuf<int64_t> tot(1);
     hipLaunchKernelGGL(k_iota, dim3(grid_for(n)), dim3(WG), 0, s, list.get(), (int)n);
     DBuf<double> lamt((size_t)depth * nblk * m2), gh((size_t)nblk * 2 * m2);
     const int maxdeg = max_span(c, n, 1, ap.ptr.get());
@@ -3063,7 +3185,7 @@ void fit_level_overlap_exact(Ctx &c, Level &L, const cs_options &o) {
                                    E.pat.col.get(), cnt.get(), nullptr, nullptr, err.get());
         CS_LAUNCH_CHECK();
         check_flags(c, err, n, "fill of a residual row");
-        mp.nnzb = scan_counts(c, cnt, n, mp.ptr, tot);
+        mp.nnzb = scan_counts(c, cnt, n, mp.ptr);
         mp.col.alloc(std::max<int64_t>(mp.nnzb, 1));
         launch_union<SRC_E, true>(s, bound, list.get(), (int)n, 1, ap.ptr.get(), ap.col.get(), E.pat.ptr.get(),
                                   E.pat.col.get(), nullptr, mp.ptr.get(), mp.col.get(), err.get());
@@ -3089,7 +3211,7 @@ void fit_level_overlap_exact(Ctx &c, Level &L, const cs_options &o) {
         check_flags(c, err, n, "fill of an overlapping residual row");
         EMat N;
         N.pat.rows = n;
-        N.pat.nnzb = scan_counts(c, cnt, n, N.pat.ptr, tot);
+        N.pat.nnzb = scan_counts(c, cnt, n, N.pat.ptr);
         N.pat.col.alloc(std::max<int64_t>(N.pat.nnzb, 1));
         N.val.alloc(std::max<int64_t>(N.pat.nnzb, 1));
         hipLaunchKernelGGL(k_ovl_union<true>, dim3((unsigned)n), dim3(WG), 0, s, n, m, L.ovl_nodes.get(),
@@ -3342,6 +3464,7 @@ void jacobi_level(Ctx &c, Level &L, const cs_options &o) {
 }
 
 void run_setup(Ctx &c, const cs_options &o) {
+    PoolScope scope;
     CS_HIP(hipEventRecord(c.ev0, c.stream));
     c.singular = 0;
     for (size_t l = 0; l + 1 < c.lv.size(); ++l) {
@@ -3359,6 +3482,7 @@ void run_setup(Ctx &c, const cs_options &o) {
 }
 
 void run_setup_sketched(Ctx &c, const cs_options &o, int sk, const double *S) {
+    PoolScope scope;
     CS_HIP(hipEventRecord(c.ev0, c.stream));
     c.singular = 0;
     for (Level &L : c.lv) {   // no exact block fit: no class statistics
@@ -3398,6 +3522,7 @@ void prescaled_blocks(Ctx &c, Level &L, float *out) {
 
 void run_setup_learned(Ctx &c, const cs_options &o, const float *lam_t) {
     // lam_t is produced on c.stream before this call; timing covers it
+    PoolScope scope;
     Level &L0 = c.lv[0];
     const int nb2 = (int)(L0.nb * L0.nb);
     L0.w.release();
