@@ -2030,53 +2030,77 @@ __global__ void k_colour_check(int B, const int32_t *__restrict__ bptr, const in
 }
 
 // ---------------------------------------------------------------------------
-// bottom level: Gauss-Jordan inversion, one pivot per launch (ping-pong)
+// direct segments: Gauss-Jordan inversion, GJ_P pivots per launch (ping-pong)
 // ---------------------------------------------------------------------------
-__global__ void k_gauss_jordan(const double *__restrict__ in, double *__restrict__ out, int n, int k) {
-    int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (e >= (int64_t)n * n) return;
-    int i = (int)(e / n), j = (int)(e % n);
-    double p = in[(int64_t)k * n + k];
-    double v;
-    if (i == k) v = (j == k) ? 1.0 / p : in[(int64_t)k * n + j] / p;
-    else {
-        double f = in[(int64_t)i * n + k];
-        v = (j == k) ? -f / p : in[e] - f * in[(int64_t)k * n + j] / p;
-    }
-    out[e] = v;
+// Pivots [k0, k0 + GJ_P) on a 32 x 32 tile of a segment (toff: offsets of the
+// segments' tiles, nact of them): the workgroup keeps the tile's entries in registers and the pivot block, the
+// pivot rows over the tile's columns and the tile's rows over the pivot columns in
+// LDS, and takes the pivots one after the other on all of them.  Every entry goes
+// through the same operations in the same order as with a launch per pivot (a
+// Schur-complement form loses digits on the ill-conditioned bottom matrices), only
+// the panels are computed once per tile; a launch per pivot was bound by its own
+// latency (256 rows: 256 launches of 3.6 us).  Segments are packed largest first:
+// those larger than k0 are a prefix.  Segment q is m[q] x m[q], row-major.
+constexpr int GJ_P = 16, GJ_T = 32;
+__device__ __forceinline__ double gj_step(bool row, bool col, double a, double f, double g, double p) {
+    if (row) return col ? 1.0 / p : g / p;
+    return col ? -f / p : a - f * g / p;
 }
-
-// One Gauss-Jordan pivot step k applied to every segment's dense matrix at
-// once; segments already past their size are copied unchanged.
-// One Gauss-Jordan step k on the segments that are still active: segments are
-// packed largest first, so the active ones are a prefix [0, nact) and their
-// entries the range [0, soff[nact]).  Segment q is m[q] x m[q], row-major.
-__global__ void k_gauss_jordan_seg(const double *__restrict__ in, double *__restrict__ out, int nact,
-                                   const int64_t *__restrict__ soff, const int32_t *__restrict__ msz, int k) {
-    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (e >= soff[nact]) return;
-    int lo = 0, hi = nact;   // segment q with soff[q] <= e < soff[q+1]
+__global__ __launch_bounds__(WG) void k_gauss_jordan_seg(const double *__restrict__ in, double *__restrict__ out,
+                                                         int nact, const int64_t *__restrict__ soff,
+                                                         const int64_t *__restrict__ toff,
+                                                         const int32_t *__restrict__ msz, int k0) {
+    __shared__ double D[GJ_P][GJ_P], R[GJ_P][GJ_T], C[GJ_T][GJ_P + 1];
+    int lo = 0, hi = nact;   // segment lo with toff[lo] <= tile < toff[lo + 1]
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (soff[mid] <= e) lo = mid;
+        if (toff[mid] <= (int64_t)blockIdx.x) lo = mid;
         else hi = mid;
     }
-    const int64_t base = soff[lo];
-    const int m = msz[lo];
-    const int loc = (int)(e - base), i = loc / m, j = loc % m;
-    const double *a = in + base;
-    const double p = a[k * m + k];
-    double v;
-    if (i == k) v = (j == k) ? 1.0 / p : a[k * m + j] / p;
-    else {
-        const double f = a[i * m + k];
-        v = (j == k) ? -f / p : a[loc] - f * a[k * m + j] / p;
+    const int m = msz[lo], tiles = (m + GJ_T - 1) / GJ_T, tile = (int)(blockIdx.x - toff[lo]);
+    const double *a = in + soff[lo];
+    const int i0 = tile / tiles * GJ_T, j0 = tile % tiles * GJ_T;
+    const int t = threadIdx.x, np = min(GJ_P, m - k0);
+    // this thread's entries: D (t / 16, t % 16); R rows t / 32 and + 8, column t % 32;
+    // C rows t / 16 and + 16, column t % 16; tile rows t / 32 + 8 u, column t % 32
+    const int dr = t >> 4, dc = t & 15, rr = t >> 5, rc = t & 31;
+    auto at = [&](int i, int j) { return i < m && j < m ? a[(int64_t)i * m + j] : 0.0; };
+    D[dr][dc] = at(k0 + dr, k0 + dc);
+    R[rr][rc] = at(k0 + rr, j0 + rc);
+    R[rr + 8][rc] = at(k0 + rr + 8, j0 + rc);
+    C[dr][dc] = at(i0 + dr, k0 + dc);
+    C[dr + 16][dc] = at(i0 + dr + 16, k0 + dc);
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = at(i0 + rr + 8 * u, j0 + rc);
+    __syncthreads();
+    for (int s = 0; s < np; ++s) {
+        const int k = k0 + s;
+        const double p = D[s][s], gR = R[s][rc], gD = D[s][dc];
+        const double d = gj_step(dr == s, dc == s, D[dr][dc], D[dr][s], gD, p);
+        const double r0 = gj_step(rr == s, j0 + rc == k, R[rr][rc], D[rr][s], gR, p);
+        const double r1 = gj_step(rr + 8 == s, j0 + rc == k, R[rr + 8][rc], D[rr + 8][s], gR, p);
+        const double c0 = gj_step(i0 + dr == k, dc == s, C[dr][dc], C[dr][s], gD, p);
+        const double c1 = gj_step(i0 + dr + 16 == k, dc == s, C[dr + 16][dc], C[dr + 16][s], gD, p);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u] = gj_step(i0 + rr + 8 * u == k, j0 + rc == k, v[u], C[rr + 8 * u][s], gR, p);
+        __syncthreads();
+        D[dr][dc] = d;
+        R[rr][rc] = r0;
+        R[rr + 8][rc] = r1;
+        C[dr][dc] = c0;
+        C[dr + 16][dc] = c1;
+        __syncthreads();
     }
-    out[e] = v;
+    double *o = out + soff[lo];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (i0 + rr + 8 * u < m && j0 + rc < m) o[(int64_t)(i0 + rr + 8 * u) * m + j0 + rc] = v[u];
 }
 
 // Final inverses into their places: packed segment q finished in buffer b1
-// when its size is odd (steps alternate a -> b -> a ...), else in b0.
+// when it took an odd number of launches (they alternate a -> b -> a ...), else in b0.
 __global__ void k_gauss_jordan_collect(int64_t tot, int nseg, const int64_t *__restrict__ soff,
                                        const int32_t *__restrict__ msz, const int64_t *__restrict__ dst_off,
                                        const double *__restrict__ b0, const double *__restrict__ b1,
@@ -2089,7 +2113,7 @@ __global__ void k_gauss_jordan_collect(int64_t tot, int nseg, const int64_t *__r
         if (soff[mid] <= e) lo = mid;
         else hi = mid;
     }
-    out[dst_off[lo] + (e - soff[lo])] = (msz[lo] & 1) ? b1[e] : b0[e];
+    out[dst_off[lo] + (e - soff[lo])] = ((msz[lo] + GJ_P - 1) / GJ_P & 1) ? b1[e] : b0[e];
 }
 
 __global__ void k_transpose_blocks64(int64_t nblk, int nb, const double *__restrict__ a, double *__restrict__ at) {
@@ -3380,7 +3404,7 @@ void factor_direct(Ctx &c, Level &L) {
     std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) {
         return L.dseg[x + 1] - L.dseg[x] > L.dseg[y + 1] - L.dseg[y];
     });
-    std::vector<int64_t> src_off(nseg + 1, 0), soff(nseg + 1, 0), dst_off(nseg);
+    std::vector<int64_t> src_off(nseg + 1, 0), soff(nseg + 1, 0), toff(nseg + 1, 0), dst_off(nseg);
     std::vector<int32_t> msz(nseg);
     for (int q = 0; q < nseg; ++q) {
         const int64_t m = L.dseg[q + 1] - L.dseg[q];
@@ -3393,25 +3417,26 @@ void factor_direct(Ctx &c, Level &L) {
         msz[t] = (int32_t)m;
         dst_off[t] = src_off[q];
         soff[t + 1] = soff[t] + m * m;
+        toff[t + 1] = toff[t] + ceil_div(m, GJ_T) * ceil_div(m, GJ_T);
         std::copy(dense.begin() + src_off[q], dense.begin() + src_off[q + 1], packed.begin() + soff[t]);
     }
     const int64_t tot = (int64_t)L.dinv.n;
     DBuf<double> a(tot), b(tot);
-    DBuf<int64_t> soff_d, dst_d;
+    DBuf<int64_t> soff_d, toff_d, dst_d;
     DBuf<int32_t> msz_d;
     a.upload(packed.data(), packed.size(), c.stream);
     soff_d.upload(soff.data(), soff.size(), c.stream);
+    toff_d.upload(toff.data(), toff.size(), c.stream);
     dst_d.upload(dst_off.data(), dst_off.size(), c.stream);
     msz_d.upload(msz.data(), msz.size(), c.stream);
-    // step k reads buffer (k even ? a : b) and writes the other one
+    // launch q reads buffer (q even ? a : b) and writes the other one
     int nact = nseg;
-    for (int k = 0; k < L.dseg_max; ++k) {
+    for (int k = 0; k < L.dseg_max; k += GJ_P) {
         while (nact > 0 && msz[nact - 1] <= k) --nact;
-        const int64_t n_el = soff[nact];
-        const double *in = (k & 1) ? b.get() : a.get();
-        double *out = (k & 1) ? a.get() : b.get();
-        hipLaunchKernelGGL(k_gauss_jordan_seg, dim3(grid_for(n_el)), dim3(WG), 0, c.stream, in, out, nact,
-                           soff_d.get(), msz_d.get(), k);
+        const bool odd = (k / GJ_P) & 1;
+        hipLaunchKernelGGL(k_gauss_jordan_seg, dim3((unsigned)toff[nact]), dim3(WG), 0, c.stream,
+                           odd ? b.get() : a.get(), odd ? a.get() : b.get(), nact, soff_d.get(), toff_d.get(),
+                           msz_d.get(), k);
     }
     hipLaunchKernelGGL(k_gauss_jordan_collect, dim3(grid_for(tot)), dim3(WG), 0, c.stream, tot, nseg, soff_d.get(),
                        msz_d.get(), dst_d.get(), a.get(), b.get(), L.dinv.get());
