@@ -405,3 +405,16 @@ def test_ridge_is_refused_where_it_does_not_apply(gpu_lib):
     o = gpu_lib.cs_options(2, 0, 1, 1, 1, 0, 0, 1e-3)
     st = s._lib.cs_setup_sketched(s._h, ctypes.byref(o), 8, ctypes.c_void_p(S.data_ptr()))
     assert st == -1 and "exact fit only" in s._lib.cs_last_error(s._h).decode()
+
+
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 31, 32, 33, 48, 63, 65, 100, 257])
+def test_direct_inverse_sizes(gpu_lib, n):
+    """The inverse of a coarsest level around the 16-pivot panels and 32 x 32
+    tiles of the elimination: a one-level V-cycle against a dense solve."""
+    rng = stream(21, TEST, n)
+    M = 4.0 * np.eye(n) + rng.uniform(-1, 1, size=(n, n)) / np.sqrt(n)   # the elimination does not pivot
+    b = rng.uniform(-1, 1, size=(n, 2))
+    s = gpu_lib.Solver([Level(sp.csr_matrix(M), 1, None)])
+    s.setup(depth=1)
+    # condition number below (4 + 2) / (4 - 2) = 3: rounding of order n eps
+    check_vec(s.vcycle(b).cpu().numpy(), np.linalg.solve(M, b), 1e-12, f"direct inverse n={n}")
