@@ -1068,6 +1068,18 @@ __device__ __forceinline__ void gm_partials(const double (&acc)[MV], int nv, dou
     }
 }
 
+// One element of the first nv basis vectors, all loads in flight before the
+// first use: with a load and its use per vector the Gram-Schmidt kernels waited
+// for the memory nv times per element.
+template <int MV>
+__device__ __forceinline__ void gm_load(const double *__restrict__ p, int64_t ld, int nv, double (&v)[MV]) {
+#pragma unroll
+    for (int i = 0; i < MV; ++i) {
+        v[i] = 0.0;
+        if (i < nv) v[i] = __builtin_nontemporal_load(p + i * ld);   // uniform
+    }
+}
+
 // h_i = (v_i, w) for i < nv
 template <typename W, int R, int MV>
 __global__ __launch_bounds__(WG) void k_gm_dots(int64_t nel, int nsys, const int32_t *__restrict__ sys_wg,
@@ -1082,10 +1094,12 @@ __global__ __launch_bounds__(WG) void k_gm_dots(int64_t nel, int nsys, const int
 #pragma unroll
     for (int i = 0; i < MV; ++i) acc[i] = 0.0;
     for (int64_t e = er.begin; e < er.end; e += er.stride) {
+        double v[MV];
+        gm_load<MV>(vt + e, ld, nv, v);
         const double we = (double)w[e];
 #pragma unroll
         for (int i = 0; i < MV; ++i)
-            if (i < nv) acc[i] += __builtin_nontemporal_load(vt + i * ld + e) * we;
+            if (i < nv) acc[i] += v[i] * we;
     }
 #pragma unroll
     for (int i = 0; i < MV; ++i)
@@ -1114,13 +1128,11 @@ __global__ __launch_bounds__(WG) void k_gm_update(int64_t nel, int nsys, const i
     }
     for (int64_t e = er.begin; e < er.end; e += er.stride) {
         double v[MV];
+        gm_load<MV>(vt + e, ld, nv, v);
         double we = (double)w[e];
 #pragma unroll
         for (int i = 0; i < MV; ++i)
-            if (i < nv) {
-                v[i] = __builtin_nontemporal_load(vt + i * ld + e);
-                we -= coef[i] * v[i];
-            }
+            if (i < nv) we -= coef[i] * v[i];
         wout[e] = we;
         if constexpr (DOTS) {
 #pragma unroll
@@ -1162,43 +1174,43 @@ __global__ __launch_bounds__(WG) void k_gm_xupdate(int64_t nel, int nsys, const 
 }
 
 // Per-system sums of GMRES partials: out[s][c] = sum over the workgroups of
-// system s of partial[b][c], c < W.  Workgroup (s, c-block of 64): wavefront
-// w of 16 sums every 16th workgroup with four independent accumulators (loads
-// in flight), then the wavefronts are added in order.  Fixed order throughout.
-__global__ __launch_bounds__(1024) void k_gm_reduce(int W, int64_t G, const int32_t *__restrict__ sys_wg,
-                                                    const double *__restrict__ partial, double *__restrict__ out) {
+// system s of partial[b][c], c < W.  Workgroup (s, c-block of 64): the lanes
+// take WP = the power of two >= min(W, 64) components of 64 / WP workgroups'
+// partials, so that few components still use whole wavefronts; each lane sums
+// with four independent accumulators (loads in flight), then the lanes and the
+// 16 wavefronts are added in order.  Fixed order throughout.  With sc also
+// sc = 1 / sqrt(sum) (0 for a zero or non-finite sum).
+__global__ __launch_bounds__(1024) void k_gm_reduce(int W, int WP, int64_t G, const int32_t *__restrict__ sys_wg,
+                                                    const double *__restrict__ partial, double *__restrict__ out,
+                                                    double *__restrict__ sc) {
     __shared__ double red[16][64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int s = blockIdx.y;
-    const int c = blockIdx.x * 64 + lane;
+    const int c = blockIdx.x * 64 + (lane & (WP - 1));
+    const int per = 64 / WP, step = 16 * per;
     const int64_t b0 = sys_wg ? sys_wg[s] : 0, b1 = sys_wg ? sys_wg[s + 1] : G;
     double v0 = 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
     if (c < W) {
-        int64_t b = b0 + wv;
-        for (; b + 48 < b1; b += 64) {
+        int64_t b = b0 + wv * per + lane / WP;
+        for (; b + 3 * step < b1; b += 4 * step) {
             v0 += partial[b * W + c];
-            v1 += partial[(b + 16) * W + c];
-            v2 += partial[(b + 32) * W + c];
-            v3 += partial[(b + 48) * W + c];
+            v1 += partial[(b + step) * W + c];
+            v2 += partial[(b + 2 * step) * W + c];
+            v3 += partial[(b + 3 * step) * W + c];
         }
-        for (; b < b1; b += 16) v0 += partial[b * W + c];
+        for (; b < b1; b += step) v0 += partial[b * W + c];
     }
-    red[wv][lane] = (v0 + v1) + (v2 + v3);
+    double v = (v0 + v1) + (v2 + v3);
+    for (int off = 32; off >= WP; off >>= 1) v += __shfl_xor(v, off, 64);
+    red[wv][lane] = v;
     __syncthreads();
-    if (wv == 0 && c < W) {
+    if (wv == 0 && lane < WP && c < W) {
         double t = 0.0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) t += red[w][lane];
         out[(int64_t)s * W + c] = t;
+        if (sc) sc[(int64_t)s * W + c] = (t > 0.0 && isfinite(t)) ? 1.0 / sqrt(t) : 0.0;
     }
-}
-
-// sc[col] = 1 / sqrt(n2[col]) (0 for a zero or non-finite norm)
-__global__ void k_gm_rscale(int ncol, const double *__restrict__ n2, double *__restrict__ sc) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncol) return;
-    const double v = n2[c];
-    sc[c] = (v > 0.0 && isfinite(v)) ? 1.0 / sqrt(v) : 0.0;
 }
 
 // out = sc * (A vt) (left GMRES: the V-cycle input, in the working precision)
@@ -2617,7 +2629,10 @@ void solve_gmres(Ctx &c, const double *b, double *x, int nrhs, double rtol, int 
     c.gm_sc.alloc((size_t)(m + 1) * ncol);
     c.gm_h.alloc((size_t)(2 * (m + 1) + 1) * ncol);
     c.gm_y.alloc((size_t)ncol * m);
-    int64_t Gp = std::min<int64_t>(std::max<int64_t>(ceil_div(nel, 4 * WG), 1), IR_GRID);
+    // four elements per thread, but fewer where that leaves the chip without two
+    // workgroups per CU (65,536 elements: 64 -> 256 workgroups)
+    int64_t Gp = std::min<int64_t>(std::max<int64_t>(ceil_div(nel, 4 * WG), std::min<int64_t>(ceil_div(nel, WG), 512)),
+                                   IR_GRID);
     const int32_t *sys_wg = nullptr;
     if (batch) {
         std::vector<int32_t> wg(nsys + 1, 0);
@@ -2649,9 +2664,11 @@ void solve_gmres(Ctx &c, const double *b, double *x, int nrhs, double rtol, int 
             constexpr int R = decltype(rc)::value;
             T *bb = reinterpret_cast<T *>(L0.w_bb);
             const T *xb = reinterpret_cast<const T *>(L0.w_xb);
-            auto reduce = [&](int W, double *out) {
+            auto reduce = [&](int W, double *out, double *rsqrt_out = nullptr) {
+                int WP = 1;
+                while (WP < W && WP < 64) WP *= 2;
                 hipLaunchKernelGGL(k_gm_reduce, dim3((unsigned)ceil_div(W, 64), (unsigned)nsys), dim3(1024), 0,
-                                   c.stream, W, Gp, sys_wg, part, out);
+                                   c.stream, W, WP, Gp, sys_wg, part, out, rsqrt_out);
                 CS_LAUNCH_CHECK();
             };
             const dim3 gg((unsigned)Gp);
@@ -2686,10 +2703,7 @@ void solve_gmres(Ctx &c, const double *b, double *x, int nrhs, double rtol, int 
                     });
                 }
                 CS_LAUNCH_CHECK();
-                reduce(R, n2);
-                hipLaunchKernelGGL(k_gm_rscale, dim3((unsigned)ceil_div(ncol, 256)), dim3(256), 0, c.stream, ncol,
-                                   n2, sc);
-                CS_LAUNCH_CHECK();
+                reduce(R, n2, sc);
                 CS_HIP(hipMemcpyAsync(c.gm_host, n2, ncol * sizeof(double), hipMemcpyDeviceToHost, c.stream));
                 CS_HIP(hipStreamSynchronize(c.stream));
             };
@@ -2803,10 +2817,7 @@ void solve_gmres(Ctx &c, const double *b, double *x, int nrhs, double rtol, int 
                                            sysp, nv, V, nel, sc, h2, (const double *)w1, vn, part);
                     });
                     CS_LAUNCH_CHECK();
-                    reduce(R, n2);
-                    hipLaunchKernelGGL(k_gm_rscale, dim3((unsigned)ceil_div(ncol, 256)), dim3(256), 0, c.stream, ncol,
-                                       n2, sc + (int64_t)(j + 1) * ncol);
-                    CS_LAUNCH_CHECK();
+                    reduce(R, n2, sc + (int64_t)(j + 1) * ncol);
                     CS_HIP(hipMemcpyAsync(c.gm_host, dh, (size_t)(2 * nv + 1) * ncol * sizeof(double),
                                           hipMemcpyDeviceToHost, c.stream));
                     CS_HIP(hipStreamSynchronize(c.stream));

@@ -206,3 +206,23 @@ def test_vcycle_after_cg_is_unaffected(gpu_lib, precision):
     x2, i2 = ref.solve(p.rhs, rtol=1e-10, maxit=100, method="cg")
     assert i1["iterations"] == i2["iterations"]
     np.testing.assert_array_equal(x1.cpu().numpy(), x2.cpu().numpy())
+
+
+# 256 elements are one workgroup of the basis-vector kernels, 131,072 the last
+# size with one element per thread, 524,288 the last below four
+@pytest.mark.parametrize("flexible", [False, True])
+@pytest.mark.parametrize("n,nrhs", [(8, 1), (16, 1), (16, 2), (32, 8), (256, 2), (256, 4), (256, 8)])
+def test_gmres_sizes_and_basis_lengths(gpu_lib, n, nrhs, flexible):
+    """Up to 20 steps in one cycle against the oracle's GMRES around the same
+    V-cycle (a depth-1 cascade, so that the cycle is long)."""
+    p = fd.poisson2d(n, nrhs=nrhs)
+    s = gpu_lib.Solver(p.levels)
+    s.setup(depth=1, n_pre=1, n_post=1)
+    pre = lambda r: s.vcycle(r).cpu().numpy()
+    kw = dict(restart=30, rtol=1e-9, maxit=20, flexible=flexible)
+    xo, ho = O.gmres(p.levels[0].A, pre, p.rhs, **kw)
+    x, info = s.solve(p.rhs, rtol=1e-9, maxit=20, method="fgmres" if flexible else "gmres", restart=30,
+                      raise_on_noconv=False)
+    assert info["iterations"] == len(ho) - 1
+    np.testing.assert_allclose(info["history"], ho, rtol=1e-6, atol=1e-13)
+    check_vec(x.cpu().numpy(), xo, 1e-8, f"GMRES {n}x{nrhs} flexible={flexible} iterate vs oracle")
