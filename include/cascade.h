@@ -346,8 +346,11 @@ cs_status cs_get_graphs(cs_ctx ctx, int32_t *on, double *eager_ms, double *graph
  * workgroup per system and right-hand side, that runs the same per-row
  * arithmetic with workgroup barriers in place of kernel boundaries, so results
  * are bit-identical to the per-level launches.  It applies to additive cascades
- * with one block size of 1, 2, 4 or 8 on the covered levels, n_pre >= 1 and
- * n_post >= 1; other hierarchies run the per-level launches.  The systems are
+ * with one block size of 1, 2, 4 or 8 on the covered levels and, with one
+ * right-hand side and no independent systems, to multicoloured ones in CS_BF16
+ * (blocks of 16; the schedule of a level takes LDS too, which leaves about 3,000
+ * rows), n_pre >= 1 and n_post >= 1; other hierarchies run the per-level
+ * launches.  The systems are
  * those of cs_set_systems where the transfers are aggregations and no row of a
  * covered level couples two of them, else there is one.  max_rows 0 switches it
  * off (the default).  One workgroup walks a system's rows 1024 at a time, so

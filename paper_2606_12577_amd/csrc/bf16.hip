@@ -20,35 +20,13 @@
 
 #include <hip/hip_ext.h>
 
+#include "bf16_device.h"
 #include "cs_internal.h"
 
 namespace cs {
 namespace {
 
 constexpr int WG = 256;
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ unsigned short f2bf(float f) {   // round to nearest even
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
-}
-__device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float((uint32_t)h << 16); }
-
-__device__ __forceinline__ void split(const float (&v)[4], bf16x4 &hi, bf16x4 &lo) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const unsigned short h = f2bf(v[t]);
-        hi[t] = (short)h;
-        lo[t] = (short)f2bf(v[t] - bf2f(h));
-    }
-}
-
-__device__ __forceinline__ f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-}
-
 // acc + sum over the blocks [e0, e1) of a row of A_ij x_j (rows 4 kg .. 4 kg + 3).
 // Blocks are taken four at a time: their block and x loads are all issued
 // before the first MFMA (a wavefront then waits once per four blocks instead
@@ -86,7 +64,6 @@ __device__ __forceinline__ f32x4 block_row_product(int e0, int e1, int lane, con
 // The row's first META_COLS blocks, whose block columns the row record holds:
 // their block and x loads all go out at once, before the first MFMA; the
 // products are summed in block order, as block_row_product does.
-constexpr int META_COLS = 5;
 __device__ __forceinline__ f32x4 block_row_head(int e0, int ne, const int (&col)[META_COLS], int lane,
                                                 const unsigned short *__restrict__ aval,
                                                 const float *__restrict__ x) {
@@ -116,7 +93,9 @@ __device__ __forceinline__ f32x4 block_row_head(int e0, int ne, const int (&col)
 
 // Multiplicative cascade step on one colour's nblk active block rows:
 // x_i <- x_i - Lambda_i (sum_j A_ij x_j - b_i), in place; ZERO: x = 0 before
-// the step, so x_i = Lambda_i b_i.  One wavefront per block row, read from a
+// the step, so x_i = Lambda_i b_i, and the launch (over the rows of all colours,
+// the step's being [z0, z1) of them) clears the other rows instead of a launch
+// of its own before it.  One wavefront per block row, read from a
 // 32-byte record {row, first block, end block, c0 | c1, c2, c3, c4} that also
 // holds the block columns of the row's first five blocks (the rest come from
 // bcol): the x gathers of a row then wait on one load instead of two
@@ -129,13 +108,19 @@ __global__ __launch_bounds__(WG) void k_bsr16_sweep(int64_t nblk, const int4 *__
                                                     const int32_t *__restrict__ bcol,
                                                     const unsigned short *__restrict__ aval,
                                                     const unsigned short *__restrict__ lam,
-                                                    const float *__restrict__ b, float *x) {
+                                                    const float *__restrict__ b, float *x, int64_t z0, int64_t z1) {
     const int lane = threadIdx.x & 63, kg = lane >> 4;
     const int64_t w = (int64_t)blockIdx.x * (WG / 64) + (threadIdx.x >> 6);
     if (w >= nblk) return;   // whole wavefront
     const int4 m = meta[2 * w];
     const int4 m2 = meta[2 * w + 1];
     const int i = m.x;
+    if constexpr (ZERO) {
+        if (w < z0 || w >= z1) {   // another colour
+            if (lane < 4) *reinterpret_cast<float4 *>(x + (int64_t)i * 16 + lane * 4) = float4{0.f, 0.f, 0.f, 0.f};
+            return;
+        }
+    }
     // b and Lambda_i do not depend on the product: their loads go out first
     const float4 bv = *reinterpret_cast<const float4 *>(b + (int64_t)i * 16 + kg * 4);
     const bf16x4 l = *reinterpret_cast<const bf16x4 *>(lam + (int64_t)i * 256 + lane * 4);
@@ -209,6 +194,7 @@ void build_bf16_level(Ctx &c, Level &L) {
     L.bsr_col.release();
     L.a16.release();
     L.bmeta.release();
+    L.h_bmeta.clear();
     L.h_bsr_ptr.clear();
     if (L.nb != 16) return;
     // block-CSR pattern of A over all block rows (host, from the scalar CSR)
@@ -255,6 +241,7 @@ void build_bf16_meta(Ctx &c, Level &L, const std::vector<int32_t> &act) {
         for (int k = 0; k < META_COLS; ++k) m[8 * q + 3 + k] = e0 + k < e1 ? cols[e0 + k] : -1;
     }
     L.bmeta.upload(m.data(), m.size(), c.stream);
+    L.h_bmeta = m;
     CS_HIP(hipStreamSynchronize(c.stream));   // the host vector goes out of scope
 }
 
@@ -282,6 +269,7 @@ double bf16_sweep_bytes(const Level &L, int colour, bool zero) {
            nblk * (512.0 + 16 * 4 * (zero ? 2.0 : 3.0));
 }
 
+// zero: from x = 0; the launch also clears the active rows of the other colours.
 void bf16_sweep(Ctx &c, const Level &L, int ell, int colour, bool reverse, bool zero, const float *b, float *x) {
     const int64_t k0 = L.cblk_ptr[colour], nblk = L.cblk_ptr[colour + 1] - k0;
     if (nblk == 0) return;
@@ -292,13 +280,14 @@ void bf16_sweep(Ctx &c, const Level &L, int ell, int colour, bool reverse, bool 
     (void)trace_begin_launch(c, zero ? CS_TRACE_SWEEP_ZERO : (L.n >= (1 << 19) ? CS_TRACE_SWEEP
                                                                                : CS_TRACE_SWEEP_SMALL),
                              bf16_sweep_bytes(L, colour, zero), &ev0, &ev1);
-    const int4 *meta = reinterpret_cast<const int4 *>(L.bmeta.get()) + 2 * k0;   // two int4 per row
+    const int4 *meta = reinterpret_cast<const int4 *>(L.bmeta.get());   // two int4 per row
+    const int64_t all = L.cblk_ptr.back();
     if (zero)
-        hipExtLaunchKernelGGL(k_bsr16_sweep<true>, dim3(gdim(nblk, WG / 64)), dim3(WG), 0, c.stream, ev0, ev1, 0,
-                              nblk, meta, L.bsr_col.get(), L.a16.get(), lam, b, x);
+        hipExtLaunchKernelGGL(k_bsr16_sweep<true>, dim3(gdim(all, WG / 64)), dim3(WG), 0, c.stream, ev0, ev1, 0,
+                              all, meta, L.bsr_col.get(), L.a16.get(), lam, b, x, k0, k0 + nblk);
     else
         hipExtLaunchKernelGGL(k_bsr16_sweep<false>, dim3(gdim(nblk, WG / 64)), dim3(WG), 0, c.stream, ev0, ev1, 0,
-                              nblk, meta, L.bsr_col.get(), L.a16.get(), lam, b, x);
+                              nblk, meta + 2 * k0, L.bsr_col.get(), L.a16.get(), lam, b, x, (int64_t)0, (int64_t)0);
     CS_LAUNCH_CHECK();
 }
 

@@ -195,6 +195,7 @@ struct Level {
     // per active block in colour order (cblk): {block row, first block, end
     // block, 0}, so a colour sweep reads one 16-byte record per block row
     DBuf<int32_t> bmeta;
+    std::vector<int32_t> h_bmeta;
     int64_t bsr_nnzb = 0;
     DBuf<unsigned short> a16, lam16, lam16T;
     DBuf<int32_t> cblk;               // active blocks grouped by colour
@@ -223,6 +224,13 @@ struct TailLevel {
     const int64_t *pptr, *tptr;
     const int32_t *plen, *pcol, *tlen, *tcol;
     const void *pval, *tval;
+    // BF16 multicoloured levels of 16x16 blocks: the schedule, block-row records,
+    // block columns, blocks and Lambda
+    int nitems, sched;   // rounds; first 16 bytes of the schedule in LDS
+    const int32_t *bmeta, *bcol;
+    const unsigned short *a16, *ar16, *lam16, *lam16T;
+    // what the cycle reads of this level, for the workgroups that warm the L2
+    struct { const void *p; int64_t bytes; } warm[12];
 };
 
 struct Trace {
@@ -301,6 +309,11 @@ struct Ctx {
     std::vector<TailLevel> tail_host;
     DBuf<int32_t> tail_sys;             // row offsets of the systems, [covered level][tail_nsys + 1]
     std::vector<int32_t> tail_sys_host;
+    DBuf<int32_t> tail_sched;           // schedules of the BF16 tail's levels
+    DBuf<unsigned short> tail_a16;      // and their copies of A
+    std::vector<int32_t> tail_sched_host;
+    int tail_zero = 0;                  // LDS offset of its block of zeros, elements
+    bool tail_b16 = false;              // the covered levels are BF16 multicoloured ones
     int tail_nsys = 1, tail_alt = 0;    // systems; LDS elements before the alternate buffer
     int64_t tail_lds = 0;               // dynamic LDS of the tail kernel, bytes
     double tail_bytes = 0.0;            // algorithmic bytes of one tail launch (trace)
@@ -380,13 +393,19 @@ void autotune(Ctx &c, int nrhs, double *ms_out);
 void tune_graphs(Ctx &c, int nrhs, double *eager_ms, double *graph_ms);
 
 // tail.hip: the small levels in one launch
-int tail_start(const Ctx &c);
+int tail_start(const Ctx &c, int nrhs = 1);
 void tail_prepare(Ctx &c, int nrhs);
 // whether the tail runs the V-cycle from level l for nrhs right-hand sides
 inline bool tail_covers(const Ctx &c, int l, int nrhs) {
     return l == c.tail_from && c.tail_gen == c.gen && c.tail_prec == c.precision && c.tail_nrhs == nrhs;
 }
 void tail_launch(Ctx &c, int nrhs, const double *b64 = nullptr, double *x64 = nullptr);
+int tail16_rounds(const Level &L);
+int64_t tail16_schedule_words(const Level &L);
+void tail16_schedule(const Level &L, uint32_t zero, std::vector<int32_t> &out);
+int64_t tail16_pack(Ctx &c, const Level &L, unsigned short *out);
+void tail16_prepare(Ctx &c);
+void tail16_launch(Ctx &c, hipEvent_t ev0, hipEvent_t ev1, const double *b64, double *x64);
 
 // solve.hip
 int tune_tail(Ctx &c, int nrhs, int64_t *rows, double *ms, int cap);

@@ -1607,14 +1607,17 @@ T *apply_cascade(Ctx &c, const Level &L, bool reverse, bool zero_start, const T 
         return cur;
     }
     // multiplicative: flattened (l, k) sequence, in place
-    if (zero_start) {
-        hipLaunchKernelGGL(k_zero<T>, dim3(grid_for(L.n_active * R)), dim3(WG), 0, c.stream, L.n_active * R, x);
-        CS_LAUNCH_CHECK();
-    }
     const int chi = L.chi;
     const int nsteps = depth * chi;
     bool bf16 = false;
     if constexpr (std::is_same<T, float>::value && R == 1) bf16 = use_bf16(c, L);
+    const int k_first = (reverse ? nsteps - 1 : 0) % chi;
+    // the BF16 sweep of the first step clears the other colours' rows itself
+    const bool cleared = bf16 && L.cblk_ptr[k_first + 1] > L.cblk_ptr[k_first];
+    if (zero_start && !cleared) {
+        hipLaunchKernelGGL(k_zero<T>, dim3(grid_for(L.n_active * R)), dim3(WG), 0, c.stream, L.n_active * R, x);
+        CS_LAUNCH_CHECK();
+    }
     // the A-reading colour sweeps of a large level run back to back: timed
     // as one run (as the additive sweeps)
     const int s_run = zero_start ? 1 : 0;

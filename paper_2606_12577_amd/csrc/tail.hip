@@ -5,25 +5,11 @@
 #include <hip/hip_ext.h>
 
 #include "cs_internal.h"
+#include "tail_device.h"
 
 namespace cs {
 
 namespace {
-
-template <typename T, int N>
-__device__ __forceinline__ void vload(const T *p, T (&o)[N]) {   // N * sizeof(T) a power of two
-    if constexpr (N * sizeof(T) >= 16) {
-        const uint4 *q = reinterpret_cast<const uint4 *>(p);
-#pragma unroll
-        for (int k = 0; k < (int)(N * sizeof(T) / 16); ++k) {
-            const uint4 u = q[k];
-            __builtin_memcpy(&o[k * (16 / sizeof(T))], &u, 16);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < N; ++k) o[k] = p[k];
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Tail V-cycle: the small levels are bound by latency (a kernel launch and
@@ -44,8 +30,9 @@ __device__ __forceinline__ void vload(const T *p, T (&o)[N]) {   // N * sizeof(T
 // launch per step, 93 us in the form with all vectors in the L2 and one
 // workgroup for all right-hand sides and systems, 51 us now; V-cycle of 16
 // systems of 64^2 to 176^2 with 4 right-hand sides: 118 us per level, 82 now.
+// Behind large levels (96^3 FP64, from 1728 rows of 8x8 blocks on) the workgroups
+// of tail_warm are worth 18 us of a 375 us V-cycle.
 // ---------------------------------------------------------------------------
-constexpr int TAIL_WG = 1024;
 // Entries per row and rows per thread held in registers, what 128 VGPRs (1024
 // threads) take without spilling: the 5-point stencil of point levels, the
 // 7-point stencil of block levels; 4 rows (4096-row levels) but for FP64 blocks.
@@ -53,36 +40,6 @@ template <int NB>
 constexpr int tail_ml() { return NB == 1 ? 5 : 7; }
 template <typename T, int NB>
 constexpr int tail_tpt() { return sizeof(T) == 8 && NB > 1 ? 2 : 4; }
-
-// LDS elements of a vector of m rows (16-byte ranges)
-template <typename T>
-__host__ __device__ __forceinline__ int tail_range(int m) { return (m + 3) & ~3; }
-
-// Dot products of SELL rows against a vector, streamed 8 entries at a time:
-// acc += sum_k val_k x[col_k - lo], k in order (as spmv_row).
-template <typename T>
-__device__ __forceinline__ T tail_row(const int32_t *__restrict__ scol, const T *__restrict__ sval, int64_t off, int len,
-                                      int lo, const T *x, T acc) {
-    for (int e0 = 0; e0 < len; e0 += 8) {
-        int cc[8];
-        T aa[8], xv[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            cc[u] = lo;
-            aa[u] = T(0);
-            if (e0 + u < len) {
-                cc[u] = scol[off + (int64_t)(e0 + u) * 64];
-                aa[u] = sval[off + (int64_t)(e0 + u) * 64];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) xv[u] = x[cc[u] - lo];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (e0 + u < len) acc += aa[u] * xv[u];
-    }
-    return acc;
-}
 
 // The rows of A that a thread owns on a level (row = thread + i * TAIL_WG of
 // the system's m active rows), in registers: values and byte offsets of the
@@ -102,10 +59,11 @@ struct TailRows {
             const int s0 = __builtin_amdgcn_readfirstlane(q >> 6);
             const int s1 = min(s0 + 1, (lo + m - 1) >> 6);
             const bool first = (q >> 6) == s0;
-            len[i] = first ? L.slen[s0] : L.slen[s1];
-            off[i] = (first ? L.sptr[s0] : L.sptr[s1]) + (q & 63);
+            len[i] = first ? gp(L.slen)[s0] : gp(L.slen)[s1];
+            off[i] = (first ? gp(L.sptr)[s0] : gp(L.sptr)[s1]) + (q & 63);
         }
-        const T *sval = static_cast<const T *>(L.sval);
+        const gptr<T> sval = gp(static_cast<const T *>(L.sval));
+        const gptr<int32_t> scol = gp(L.scol);
 #pragma unroll
         for (int i = 0; i < TPT; ++i) {
             const int own = min((int)threadIdx.x + i * TAIL_WG, m - 1);
@@ -114,7 +72,7 @@ struct TailRows {
                 int cc = own;
                 v[i][u] = T(0);
                 if (u < len[i]) {
-                    cc = L.scol[off[i] + (int64_t)u * 64] - lo;
+                    cc = scol[off[i] + (int64_t)u * 64] - lo;
                     v[i][u] = sval[off[i] + (int64_t)u * 64];
                 }
                 c[i][u] = (uint32_t)cc * sizeof(T);
@@ -155,10 +113,23 @@ __device__ __forceinline__ void tail_relax(bool valid, int row, T res, T &xo, co
     if (valid) xout[row] = xo;
 }
 
+// The row's entries of Lambda (16-byte loads where a row has as many).
 template <typename T, int NB>
 __device__ __forceinline__ void tail_lam(const T *lam, int lo, int row, int m, T (&lr)[NB]) {
     const int q = lo + min(row, m - 1);
-    vload<T, NB>(lam + (int64_t)(q / NB) * (NB * NB) + (q % NB) * NB, lr);
+    const gptr<T> p = gp(lam) + (int64_t)(q / NB) * (NB * NB) + (q % NB) * NB;
+    if constexpr (NB * sizeof(T) >= 16) {
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        const auto v = (const __attribute__((address_space(1))) u4 *)p;
+#pragma unroll
+        for (int k = 0; k < (int)(NB * sizeof(T) / 16); ++k) {
+            const u4 u = v[k];
+            __builtin_memcpy(&lr[k * (16 / sizeof(T))], &u, 16);
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < NB; ++c) lr[c] = p[c];
+    }
 }
 
 // Lambda of sweep q of a visit: the cascade's steps in order, or (rf) in
@@ -227,7 +198,7 @@ __device__ __forceinline__ void tail_smooth_stream(const TailLevel &L, int lo, i
             if (valid) {
                 r = -b[row];
                 if (!(zero && q == 0)) {
-                    r = tail_row<T>(L.scol, sval, L.sptr[g >> 6] + (g & 63), L.slen[g >> 6], lo, cur, r);
+                    r = tail_row<T>(L.scol, sval, gp(L.sptr)[g >> 6] + (g & 63), gp(L.slen)[g >> 6], lo, cur, r);
                     xo = cur[row];
                 }
             }
@@ -240,7 +211,7 @@ __device__ __forceinline__ void tail_smooth_stream(const TailLevel &L, int lo, i
     if (res)
         for (int row = threadIdx.x; row < m; row += TAIL_WG) {
             const int g = lo + row;
-            alt[row] = tail_row<T>(L.scol, sval, L.sptr[g >> 6] + (g & 63), L.slen[g >> 6], lo, x, -b[row]);
+            alt[row] = tail_row<T>(L.scol, sval, gp(L.sptr)[g >> 6] + (g & 63), gp(L.slen)[g >> 6], lo, x, -b[row]);
         }
 }
 
@@ -257,56 +228,6 @@ __device__ __forceinline__ void tail_visit(const TailLevel &L, int lo, int m, co
         tail_smooth<T, NB, 1>(L, lo, m, b, x, alt, cur, nxt, ns, rf, zero, res);
 }
 
-// Rows [a, m) of the system's direct segments: x = A_seg^{-1} b with FP64
-// accumulation, a wavefront per row (as direct_row), four rows at a time.
-template <typename T>
-__device__ __forceinline__ void tail_direct(const TailLevel &L, int lo, int a, int m, const T *b, T *x) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    constexpr int NW = TAIL_WG / 64, U = 4;
-    for (int i0 = a + wv; i0 < m; i0 += NW * U) {
-        double acc[U];
-        const double *row[U];
-        int s[U], n[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            acc[u] = 0.0;
-            const int i = i0 + u * NW;
-            row[u] = L.dinv;
-            s[u] = n[u] = 0;
-            if (i < m) {
-                int p = 0, h = L.nseg - 1;   // segment p with dseg[p] <= lo + i < dseg[p + 1]
-                while (p < h) {
-                    const int mid = (p + h + 1) >> 1;
-                    if (L.dseg[mid] <= lo + i) p = mid;
-                    else h = mid - 1;
-                }
-                s[u] = (int)(L.dseg[p] - lo);
-                n[u] = (int)(L.dseg[p + 1] - L.dseg[p]);
-                row[u] = L.dinv + L.dinv_off[p] + (int64_t)(i - s[u]) * n[u];
-            }
-        }
-        const int nmax = max(max(n[0], n[1]), max(n[2], n[3]));
-        for (int j = lane; j < nmax; j += 64) {
-            double av[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) av[u] = j < n[u] ? row[u][j] : 0.0;
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (j < n[u]) acc[u] += av[u] * (double)b[s[u] + j];
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) acc[u] += __shfl_xor(acc[u], off, 64);
-        }
-        if (lane == 0) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (i0 + u * NW < m) x[i0 + u * NW] = (T)acc[u];
-        }
-    }
-}
-
 // Alg. 1 from tab[0] (its right-hand side in global memory, [n][R]: tab[0].bb,
 // or the FP64 vector b64) to the last entry; the result in tab[0].xb, or x64.  Workgroup (system, right-hand side).
 // sys: [nlev][nsys + 1] row offsets of the systems on every level.  LDS: x and
@@ -321,7 +242,11 @@ __global__ __launch_bounds__(TAIL_WG) void k_tail_vcycle(const TailLevel *__rest
     extern __shared__ __align__(16) unsigned char tail_lds[];
     T *const base = reinterpret_cast<T *>(tail_lds);
     T *const alt = base + alt_off;
-    const int s = blockIdx.x, k = blockIdx.y;
+    if ((int)blockIdx.x >= nsys * R) {
+        tail_warm(tab, nlev, nsys * R);
+        return;
+    }
+    const int s = blockIdx.x % nsys, k = blockIdx.x / nsys;
     // x_l at x, b_l at x + m (m rows on the level, up to 16-byte ranges)
     int last = 0;   // the system's last level: nothing of it is smoothed there
     T *x = base;
@@ -329,7 +254,7 @@ __global__ __launch_bounds__(TAIL_WG) void k_tail_vcycle(const TailLevel *__rest
         const TailLevel &L = tab[0];
         const int lo = sys[s], m = sys[s + 1] - lo;
         T *b = x + tail_range<T>(m);
-        const T *gb = static_cast<const T *>(L.bb);
+        const gptr<T> gb = gp(static_cast<const T *>(L.bb));
         for (int r = threadIdx.x; r < m; r += TAIL_WG) {
             const int64_t e = (int64_t)(lo + r) * R + k;
             b[r] = b64 ? (T)b64[e] : gb[e];
@@ -358,7 +283,7 @@ __global__ __launch_bounds__(TAIL_WG) void k_tail_vcycle(const TailLevel *__rest
             if (L.agg_k > 0) {
                 for (int u = 0; u < L.agg_k; ++u) v += alt[I * L.agg_k + u];
             } else {
-                v = tail_row<T>(L.tcol, static_cast<const T *>(L.tval), L.tptr[I >> 6] + (I & 63), L.tlen[I >> 6], 0,
+                v = tail_row<T>(L.tcol, static_cast<const T *>(L.tval), gp(L.tptr)[I >> 6] + (I & 63), gp(L.tlen)[I >> 6], 0,
                                 alt, v);
             }
             bn[I] = v * rs;
@@ -380,15 +305,15 @@ __global__ __launch_bounds__(TAIL_WG) void k_tail_vcycle(const TailLevel *__rest
             T v = x[row];
             if (L.agg_k > 0) v -= xc[row >> sh];
             else
-                v -= tail_row<T>(L.pcol, static_cast<const T *>(L.pval), L.pptr[row >> 6] + (row & 63),
-                                 L.plen[row >> 6], 0, xc, T(0));
+                v -= tail_row<T>(L.pcol, static_cast<const T *>(L.pval), gp(L.pptr)[row >> 6] + (row & 63),
+                                 gp(L.plen)[row >> 6], 0, xc, T(0));
             cur[row] = v;
         }
         __syncthreads();
         tail_visit<T, NB>(L, lo, act, b, x, alt, cur, cur == x ? alt : x, ns, 0, false, false);
     }
     const int lo = sys[s], m = sys[s + 1] - lo;
-    T *gx = static_cast<T *>(tab[0].xb);
+    auto gx = (__attribute__((address_space(1))) T *)static_cast<T *>(tab[0].xb);
     for (int r = threadIdx.x; r < m; r += TAIL_WG) {
         const int64_t e = (int64_t)(lo + r) * R + k;
         if (x64) x64[e] = (double)x[r];
@@ -411,6 +336,12 @@ template <typename T>
 const T *pick(const DBuf<double> &d, const DBuf<float> &f) {
     if constexpr (std::is_same<T, double>::value) return d.get();
     else return f.get();
+}
+
+template <typename T>
+size_t pick_n(const DBuf<double> &d, const DBuf<float> &f) {
+    if constexpr (std::is_same<T, double>::value) return d.n;
+    else return f.n;
 }
 
 }  // namespace
@@ -476,28 +407,43 @@ int64_t tail_elements(const std::vector<std::vector<int32_t>> &rng, int from, in
 
 }  // namespace
 
+static bool tail_b16(const Ctx &c) { return c.opt.mode == CS_MULTIPLICATIVE && c.precision == CS_BF16; }
+
+// LDS bytes of the BF16 tail beside the vectors: a block of zeros and the schedules.
+static int64_t tail16_extra(const Ctx &c, bool b16, int from) {
+    int64_t n = 0;
+    for (size_t l = from; b16 && l + 1 < c.lv.size(); ++l) n += tail16_schedule_words(c.lv[l]) * 4;
+    return b16 ? n + 64 : 0;
+}
+
 // The levels the tail kernel covers: the first level l (the finest included)
 // from which every level has at most c.tail_rows rows, every smoothed one is
 // additive (no overlapping blocks) with one common block size of 1, 2, 4 or 8,
 // the cycle pre- and post-smooths, and a system's vectors on all covered levels
-// fit a workgroup's LDS; -1 when there is none.
-int tail_start(const Ctx &c) {
+// fit a workgroup's LDS; -1 when there is none.  Multicoloured levels are
+// covered where the sweeps run in BF16 (16x16 blocks, one right-hand side, no
+// direct segments above the last level).
+int tail_start(const Ctx &c, int nrhs) {
     const int nl = (int)c.lv.size();
-    if (c.tail_rows <= 0 || nl < 2 || c.opt.mode != CS_ADDITIVE || c.opt.n_pre < 1 || c.opt.n_post < 1) return -1;
+    if (c.tail_rows <= 0 || nl < 2 || c.opt.n_pre < 1 || c.opt.n_post < 1) return -1;
     const int64_t nb = c.lv[nl - 2].nb;
-    if (nb != 1 && nb != 2 && nb != 4 && nb != 8) return -1;
+    const bool b16 = tail_b16(c);
+    if (b16 ? nrhs != 1 : (c.opt.mode != CS_ADDITIVE || (nb != 1 && nb != 2 && nb != 4 && nb != 8))) return -1;
     int from = -1;
     for (int l = nl - 1; l >= 0; --l) {
         const Level &V = c.lv[l];
         bool ok = V.n <= c.tail_rows && !V.ovl_m;
         if (l + 1 < nl) ok = ok && V.depth >= 1 && V.nb == nb && V.n_active > 0;
+        if (l + 1 < nl && b16)
+            ok = ok && use_bf16(c, V) && !V.h_bmeta.empty() && V.lam16.get() && V.n_active == V.n;
         if (!ok) break;
         from = l;
     }
     if (from < 0 || from >= nl - 1) return -1;
     const auto rng = tail_systems(c, from);
+    if (b16 && rng[0].size() != 2) return -1;   // one system
     const int64_t es = c.precision == CS_FP64 ? 8 : 4, lim = tail_lds_limit(c);
-    while (from < nl - 1 && tail_elements(rng, from, nullptr) * es > lim) ++from;
+    while (from < nl - 1 && tail_elements(rng, from, nullptr) * es + tail16_extra(c, b16, from) > lim) ++from;
     return from < nl - 1 ? from : -1;
 }
 
@@ -506,10 +452,26 @@ namespace {
 template <typename T>
 void tail_table(Ctx &c, int nrhs) {
     if (c.tail_gen == c.gen && c.tail_prec == c.precision && c.tail_nrhs == nrhs) return;
-    const int from = tail_start(c);
+    const int from = tail_start(c, nrhs);
     c.tail_from = from;
     if (from < 0) return;
+    c.tail_b16 = tail_b16(c);
     const auto rng = tail_systems(c, from);
+    c.tail_sched_host.clear();
+    int64_t alt = 0;
+    const int64_t el = tail_elements(rng, from, &alt);   // vectors of the levels, then (from alt on) one more
+    if (c.tail_b16) {
+        for (size_t l = from; l + 1 < c.lv.size(); ++l)
+            tail16_schedule(c.lv[l], (uint32_t)(el - alt) * 4, c.tail_sched_host);
+        c.tail_sched.upload(c.tail_sched_host.data(), c.tail_sched_host.size(), c.stream);
+    }
+    int64_t soff = 0;
+    int64_t aoff = 0;
+    if (c.tail_b16) {
+        for (size_t l = from; l + 1 < c.lv.size(); ++l) aoff += tail16_pack(c, c.lv[l], nullptr);
+        c.tail_a16.alloc(aoff);
+        aoff = 0;
+    }
     std::vector<TailLevel> tab;
     std::vector<int32_t> sys;
     const double es = sizeof(T), vr = (double)nrhs * es;
@@ -520,16 +482,37 @@ void tail_table(Ctx &c, int nrhs) {
         sys.insert(sys.end(), rng[l].begin(), rng[l].end());
         bytes += (double)L.dinv.n * 8.0 + 2.0 * (L.n - L.n_active) * vr;
         TailLevel t{};
+        int nw = 0;
+        auto warm = [&](const void *p, int64_t n) {
+            if (p && n > 0) t.warm[nw++] = {p, n};
+        };
         if (l + 1 < c.lv.size()) {
-            const double A = L.act_nnz * (es + 4.0), lamb = (double)L.n_active * L.nb * es;
+            const double A = L.act_nnz * (es + 4.0), lamb = (double)L.n_active * L.nb * (c.tail_b16 ? 2.0 : es);
+            const double As = c.tail_b16 ? (double)L.bsr_nnzb * 512.0 : A;   // what the sweeps read
             const double v = (double)L.n_active * vr, sweeps = (double)(c.opt.n_pre + c.opt.n_post) * L.depth;
-            bytes += (lamb + 2.0 * v) + (sweeps - 1.0) * (A + lamb + 3.0 * v);   // the first from zero
+            bytes += (lamb + 2.0 * v) + (sweeps - 1.0) * (As + lamb + 3.0 * v);   // the first from zero
             bytes += A + 2.0 * v + 2.0 * (double)L.nc * vr + (agg ? 0.0 : 2.0 * L.p_nnz * (es + 4.0));   // transfers
             t.lam = pick<T>(L.lam64, L.lam32);
             t.lamT = pick<T>(L.lam64T, L.lam32T);
             for (int64_t r = 0; r < L.n_active; ++r)
                 t.max_len = std::max(t.max_len, (int)(L.h_ptr[r + 1] - L.h_ptr[r]));
-            if (!agg) {
+            if (c.tail_b16) {
+                t.nitems = tail16_rounds(L);
+                t.sched = (int)(soff / 4);
+                soff += tail16_schedule_words(L);
+                t.bmeta = L.bmeta.get();
+                t.bcol = L.bsr_col.get();
+                t.a16 = L.a16.get();
+                t.ar16 = c.tail_a16.get() + aoff;
+                const int64_t na = tail16_pack(c, L, c.tail_a16.get() + aoff);
+                aoff += na;
+                warm(t.ar16, na * 2);
+                warm(L.lam16.get(), (int64_t)L.lam16.n * 2);
+                if (c.opt.order == CS_RF) warm(L.lam16T.get(), (int64_t)L.lam16T.n * 2);
+                t.lam16 = L.lam16.get();
+                t.lam16T = L.lam16T.get();
+            }
+            if (!agg || c.tail_b16) {
                 t.pptr = L.psell.slice_ptr.get();
                 t.plen = L.psell.slice_len.get();
                 t.pcol = L.psell.col.get();
@@ -551,14 +534,29 @@ void tail_table(Ctx &c, int nrhs) {
         t.depth = L.depth;
         t.agg_k = agg ? L.agg_k : 0;
         t.r_scale = L.r_scale;
+        if (l + 1 < c.lv.size()) {
+            warm(t.sval, (int64_t)pick_n<T>(L.sell.val64, L.sell.val32) * sizeof(T));
+            warm(t.scol, (int64_t)L.sell.col.n * 4);
+            if (!c.tail_b16) {
+                warm(t.lam, t.nbl * L.depth * (int64_t)sizeof(T));
+                if (c.opt.order == CS_RF) warm(t.lamT, t.nbl * L.depth * (int64_t)sizeof(T));
+            }
+            if (t.pptr) {
+                warm(t.tval, (int64_t)pick_n<T>(L.ptsell.val64, L.ptsell.val32) * sizeof(T));
+                warm(t.tcol, (int64_t)L.ptsell.col.n * 4);
+                warm(t.pval, (int64_t)pick_n<T>(L.psell.val64, L.psell.val32) * sizeof(T));
+                warm(t.pcol, (int64_t)L.psell.col.n * 4);
+            }
+        }
+        warm(L.dinv.get(), (int64_t)L.dinv.n * 8);
         t.nseg = L.dseg.size() > 1 ? (int)L.dseg.size() - 1 : 0;
         t.dseg = L.dseg_d.get();
         t.dinv_off = L.dinv_off.get();
         t.dinv = L.dinv.get();
         tab.push_back(t);
     }
-    int64_t alt = 0;
-    c.tail_lds = tail_elements(rng, from, &alt) * sizeof(T);
+    c.tail_lds = el * sizeof(T) + tail16_extra(c, c.tail_b16, from);
+    c.tail_zero = (int)el;
     c.tail_alt = (int)alt;
     c.tail_nsys = (int)rng[from].size() - 1;
     c.tail_host = tab;
@@ -566,7 +564,8 @@ void tail_table(Ctx &c, int nrhs) {
     c.tail_bytes = bytes;
     c.tail_tab.upload(c.tail_host.data(), c.tail_host.size(), c.stream);
     c.tail_sys.upload(c.tail_sys_host.data(), c.tail_sys_host.size(), c.stream);
-    tail_dispatch((int)c.lv[from].nb, [&](auto nbc) {
+    if (c.tail_b16) tail16_prepare(c);
+    else tail_dispatch((int)c.lv[from].nb, [&](auto nbc) {
         constexpr int NB = decltype(nbc)::value;
         CS_HIP(   // more than 64 KB of dynamic LDS has to be asked for
             hipFuncSetAttribute(reinterpret_cast<const void *>(&k_tail_vcycle<T, NB>),
@@ -581,9 +580,15 @@ template <typename T>
 void launch(Ctx &c, int nrhs, const double *b64, double *x64) {
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     (void)trace_begin_launch(c, CS_TRACE_TAIL, c.tail_bytes, &ev0, &ev1);
+    if (c.tail_b16) {
+        tail16_launch(c, ev0, ev1, b64, x64);
+        return;
+    }
+    // workgroups that warm the L2 where the cycle's own few come after other levels
+    const unsigned n = (unsigned)(c.tail_nsys * nrhs);
     tail_dispatch((int)c.lv[c.tail_from].nb, [&](auto nbc) {
         constexpr int NB = decltype(nbc)::value;
-        hipExtLaunchKernelGGL((k_tail_vcycle<T, NB>), dim3(c.tail_nsys, nrhs), dim3(TAIL_WG), (unsigned)c.tail_lds,
+        hipExtLaunchKernelGGL((k_tail_vcycle<T, NB>), dim3(n <= 8 && c.tail_from > 0 ? 8 * (1 + TAIL_HELPERS) : n), dim3(TAIL_WG), (unsigned)c.tail_lds,
                               c.stream, ev0, ev1, 0, (const TailLevel *)c.tail_tab.get(),
                               (int)c.lv.size() - c.tail_from, c.tail_nsys, (const int32_t *)c.tail_sys.get(), nrhs,
                               c.opt.n_pre, c.opt.n_post, c.opt.order == CS_RF ? 1 : 0, c.tail_alt, b64, x64);

@@ -221,3 +221,62 @@ def test_tail_systems_of_ragged_sizes(gpu_lib):
         assert s.tail()[1] >= 0
         np.testing.assert_array_equal(s.vcycle(bt.rhs).cpu().numpy(), x0)
     s.close()
+
+
+def _nine_point_blocks(grids):
+    """Levels of 16x16 blocks on g x g grids with nine-point block coupling (rows
+    of 4, 6 and 9 blocks), four colours, 2x2 aggregation between the grids."""
+    import scipy.sparse as sp
+
+    from synth.problem import Level
+    from synth.rng import TEST, stream
+    rng = stream(31, TEST, grids[0])
+    near = rng.uniform(-1, 1, size=(16, 16)) / 64
+    diag = 2.0 * np.eye(16) + rng.uniform(-1, 1, size=(16, 16)) / 16
+    levels = []
+    for l, g in enumerate(grids):
+        t = sp.diags([1.0, 1.0, 1.0], [-1, 0, 1], shape=(g, g))
+        nine = sp.kron(t, t)
+        A = sp.kron(nine - sp.eye(g * g), near) + sp.kron(sp.eye(g * g), diag)
+        colour = (2 * (np.arange(g)[:, None] % 2) + np.arange(g)[None, :] % 2).astype(np.int32).ravel()
+        P = None
+        if l + 1 < len(grids):
+            a = sp.csr_matrix((np.ones(g), (np.arange(g), np.arange(g) // 2)), shape=(g, g // 2))
+            P = sp.csr_matrix(sp.kron(sp.kron(a, a), sp.eye(16)))
+        levels.append(Level(sp.csr_matrix(A), 16, P, 0.25, colour))
+    return levels
+
+
+# 2 to 12 blocks a side: colours of 1 to 36 rows for 16 wavefronts
+@pytest.mark.parametrize("order,n_pre,n_post,depth", [("FF", 1, 1, 3), ("RF", 1, 1, 2), ("RF", 2, 1, 1)])
+@pytest.mark.parametrize("blocks,grids", [("sipg", (8,)), ("sipg", (12,)), ("nine_point", (2, 1)), ("nine_point", (4, 2)),
+                                          ("nine_point", (8, 4, 2)), ("nine_point", (12, 6, 3))])
+def test_tail_bf16_multicoloured(gpu_lib, blocks, grids, order, n_pre, n_post, depth):
+    """The BF16 multicoloured levels in one launch: bit-identical with a launch
+    per colour step, from a whole cycle or its coarse part, in a solve and under
+    graph replay; more right-hand sides take the per-level launches."""
+    from synth import dg
+    levels = dg.sipg_q3(grids[0]).levels if blocks == "sipg" else _nine_point_blocks(grids)
+    s = gpu_lib.Solver(levels)
+    s.setup(depth=depth, mode="multiplicative", order=order, n_pre=n_pre, n_post=n_post, ridge=1e-3, precision="bf16")
+    b = np.random.default_rng(5).uniform(-1, 1, size=(levels[0].n, 1))
+    x0 = _vcycle(s, b, 0)
+    for l, lv in enumerate(levels[:-1]):
+        x1 = _vcycle(s, b, lv.n)
+        assert s.tail() == (lv.n, l)
+        np.testing.assert_array_equal(x1, x0)
+        np.testing.assert_array_equal(_vcycle(s, b, lv.n), x0)
+    kw = dict(rtol=1e-8, maxit=6, raise_on_noconv=False)
+    s.set_tail(0)
+    xa, ia = s.solve(b, **kw)
+    b2 = np.hstack([b, 2 * b])
+    y0 = s.vcycle(b2).cpu().numpy()
+    s.set_tail(levels[0].n)
+    np.testing.assert_array_equal(s.vcycle(b2).cpu().numpy(), y0)
+    for graphs in (False, True):
+        s.set_graphs(graphs)
+        for _ in range(3):
+            xb, ib = s.solve(b, **kw)
+            assert ib["iterations"] == ia["iterations"]
+            np.testing.assert_array_equal(xb.cpu().numpy(), xa.cpu().numpy())
+    s.close()
