@@ -27,6 +27,7 @@ namespace cs {
 namespace {
 
 constexpr int WG = 256;
+constexpr int64_t DEEP_SLICES = 1024;   // slices up to which long rows are loaded whole
 constexpr int64_t IR_GRID = 1024;   // workgroup cap of the outer-solver kernels (4 per CU)
 constexpr int64_t SMALL_SLICES = 8192;   // below this many 64-row slices a level counts as small
 
@@ -190,6 +191,40 @@ __device__ __forceinline__ void spmv_row(const int32_t *__restrict__ scol, const
     }
 }
 
+// Long rows of small levels (deep_rows): a wavefront per SIMD at most, so nothing
+// hides the two latencies (entry, then x) of every chunk of eight; here up to 32
+// entries, then their 32 gathers, are in flight, added in the same order.  A
+// slice's length is uniform; beyond it the last entry is loaded again.
+template <typename T, int R, int D>
+__device__ __forceinline__ void spmv_deep(const int32_t *__restrict__ scol, const T *__restrict__ sval, int64_t off,
+                                          int n, const T *x, T (&acc)[R]) {
+    int cc[D];
+    T aa[D];
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+        const int64_t o = off + (int64_t)(u < n ? u : n - 1) * 64;
+        cc[u] = scol[o];
+        aa[u] = sval[o];
+    }
+    T xv[D][R];
+#pragma unroll
+    for (int u = 0; u < D; ++u) vload<T, R>(x + (int64_t)cc[u] * R, xv[u]);
+#pragma unroll
+    for (int u = 0; u < D; ++u)
+        if (u < n) {
+#pragma unroll
+            for (int k = 0; k < R; ++k) acc[k] += aa[u] * xv[u][k];
+        }
+}
+template <typename T, int R>
+__device__ __forceinline__ void spmv_row_deep(const int32_t *__restrict__ scol, const T *__restrict__ sval,
+                                              int64_t off, int len_, const T *x, T (&acc)[R]) {
+    const int len = __builtin_amdgcn_readfirstlane(len_);
+    int e = 0;
+    for (; len - e > 16; e += 32) spmv_deep<T, R, 32>(scol, sval, off + (int64_t)e * 64, min(len - e, 32), x, acc);
+    if (len > e) spmv_deep<T, R, 16>(scol, sval, off + (int64_t)e * 64, len - e, x, acc);
+}
+
 // One cascade sweep over 4 SELL slices (256 rows) per workgroup.
 //   ZERO:   x_in = 0, so x_out = Lambda b (A is not read)
 //   ROWMAP: rows come from a colour list and x is updated in place
@@ -294,7 +329,7 @@ __device__ __forceinline__ void sweep_store(T *xout, double *acc, int64_t row, c
 
 // One tile (WGS/64 slices) of a cascade sweep; red: LDS of WGS * R values
 // (block levels), rewritten per tile.
-template <typename T, int NB, int R, bool ZERO, bool ROWMAP, bool PROL, int WGS, bool ACC = false>
+template <typename T, int NB, int R, bool ZERO, bool ROWMAP, bool PROL, int WGS, bool ACC = false, bool DEEP = false>
 __device__ __forceinline__ void sweep_tile(int64_t tile, int64_t nrows, int64_t nslices,
                                            const int32_t *__restrict__ rows, const int64_t *__restrict__ sptr,
                                            const int32_t *__restrict__ slen, const int32_t *__restrict__ scol,
@@ -330,7 +365,9 @@ __device__ __forceinline__ void sweep_tile(int64_t tile, int64_t nrows, int64_t 
         vload_nt<T, R>(b + row * R, bb);
 #pragma unroll
         for (int k = 0; k < R; ++k) res[k] = -bb[k];
-        if constexpr (!ZERO) {
+        if constexpr (DEEP) {
+            spmv_row_deep<T, R>(scol, sval, sptr[slice] + lane, slen[slice], xin, res);
+        } else if constexpr (!ZERO) {
             if constexpr (NB > 1 && NB <= 8 && !ROWMAP && sizeof(T) * R >= 16)
                 spmv_row_blk<T, R, PROL, NB>(scol, sval, sptr[slice] + lane, slen[slice], xin, xc, agg_k, row,
                                              lane, xo, res);
@@ -370,7 +407,7 @@ __device__ __forceinline__ void sweep_tile(int64_t tile, int64_t nrows, int64_t 
     }
 }
 
-template <typename T, int NB, int R, bool ZERO, bool ROWMAP, bool PROL, int WGS, bool ACC = false>
+template <typename T, int NB, int R, bool ZERO, bool ROWMAP, bool PROL, int WGS, bool ACC = false, bool DEEP = false>
 __global__ __launch_bounds__(WGS) void k_sweep(int64_t nrows, int64_t nslices, const int32_t *__restrict__ rows,
                                                const int64_t *__restrict__ sptr, const int32_t *__restrict__ slen,
                                                const int32_t *__restrict__ scol, const T *__restrict__ sval,
@@ -380,8 +417,8 @@ __global__ __launch_bounds__(WGS) void k_sweep(int64_t nrows, int64_t nslices, c
     __shared__ T red[NB > 1 ? WGS * R : 1];
     const Tiles tl = my_tiles((nslices + SPW - 1) / SPW);
     for (int64_t tile = tl.t; tile < tl.end; tile += tl.step)
-        sweep_tile<T, NB, R, ZERO, ROWMAP, PROL, WGS, ACC>(tile, nrows, nslices, rows, sptr, slen, scol, sval, lam,
-                                                           b, xin, xout, xc, agg_k, red, acc);
+        sweep_tile<T, NB, R, ZERO, ROWMAP, PROL, WGS, ACC, DEEP>(tile, nrows, nslices, rows, sptr, slen, scol, sval,
+                                                                 lam, b, xin, xout, xc, agg_k, red, acc);
 }
 
 // r = A x - b over SELL rows (natural order); blockDim / 64 slices per workgroup
@@ -1425,6 +1462,13 @@ const double *pval<double>(const Level &L, bool tr) { return tr ? L.pt_val64.get
 template <>
 const float *pval<float>(const Level &L, bool tr) { return tr ? L.pt_val32.get() : L.p_val32.get(); }
 
+// Sweeps that take spmv_row_deep: rows longer than one chunk of eight on average
+// (8x8 blocks, up to two right-hand sides: what the registers hold), and no more
+// slices than the chip has SIMDs.  FP64, 27 entries per row, two right-hand sides:
+// 13,824 rows 6.0 -> 4.8 us, 1,728 rows 5.3 -> 4.9; 110,592 rows (1,728 slices)
+// 11.0 in chunks, 11.3 whole.  Residual and transfers gained nothing from it.
+inline bool deep_rows(int64_t nslices, int64_t nrows, int64_t nnz) { return nslices <= DEEP_SLICES && nnz > 8 * nrows; }
+
 // Algorithmic bytes of one sweep launch: A's entries with their column index
 // (none from a zero guess), the Lambda rows, b and x_out, x_in (all rows of x
 // for a colour), and x_c when the interpolation is fused in.
@@ -1455,6 +1499,8 @@ void launch_sweep(Ctx &c, const Level &L, const Sell &S, bool rowmap, bool zero,
     if (L.tune_grid > 0 && (int64_t)G > L.tune_grid) G = (unsigned)L.tune_grid;
     if (G == 0) return;
     const bool prol = xc != nullptr;
+    bool deep = false;
+    if constexpr (R <= 2) deep = !acc && !rowmap && !zero && !prol && L.nb == 8 && deep_rows(nslices, nrows, nnz);
     // trace classes by level size (not by the launch shape the autotuner picks)
     const bool large = nslices >= SMALL_SLICES;
     const int cls = acc ? CS_TRACE_REFINE   // it carries the refinement's update
@@ -1488,6 +1534,19 @@ void launch_sweep(Ctx &c, const Level &L, const Sell &S, bool rowmap, bool zero,
             CS_SWEEP(true, false, false, nullptr);
         } else if (prol) {
             CS_SWEEP(false, false, true, nullptr);
+        } else if (deep) {
+            if constexpr (R <= 2 && NB == 8) {
+                if (small)
+                    hipExtLaunchKernelGGL((k_sweep<T, NB, R, false, false, false, 64, false, true>), dim3(G), dim3(64), 0,
+                                          c.stream, ev0, ev1, 0, nrows, nslices, nullptr, S.slice_ptr.get(),
+                                          S.slice_len.get(), S.col.get(), sell_val<T>(S), lam, b, xin, xout, xc, agg_k,
+                                          acc);
+                else
+                    hipExtLaunchKernelGGL((k_sweep<T, NB, R, false, false, false, WG, false, true>), dim3(G), dim3(WG), 0,
+                                          c.stream, ev0, ev1, 0, nrows, nslices, nullptr, S.slice_ptr.get(),
+                                          S.slice_len.get(), S.col.get(), sell_val<T>(S), lam, b, xin, xout, xc, agg_k,
+                                          acc);
+            }
         } else {
             CS_SWEEP(false, false, false, nullptr);
         }

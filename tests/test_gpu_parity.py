@@ -418,3 +418,33 @@ def test_direct_inverse_sizes(gpu_lib, n):
     s.setup(depth=1)
     # condition number below (4 + 2) / (4 - 2) = 3: rounding of order n eps
     check_vec(s.vcycle(b).cpu().numpy(), np.linalg.solve(M, b), 1e-12, f"direct inverse n={n}")
+
+
+@pytest.mark.parametrize("precision,nrhs", [("fp64", 1), ("fp64", 2), ("fp64", 4), ("fp32", 1), ("fp32", 2)])
+def test_sweeps_over_long_rows(gpu_lib, precision, nrhs):
+    """Sweeps of 8x8 blocks over slices of 64 rows with 9 to 70 entries (around the
+    16 and 32 that are loaded whole) and a last slice of 8 rows, against the
+    sweep in numpy with the same Lambda."""
+    lengths = [9, 15, 16, 17, 31, 32, 33, 47, 48, 49, 64, 65, 70, 8]
+    n = 64 * (len(lengths) - 1) + 8
+    rng = stream(22, TEST, nrhs)
+    rows, cols, vals = [], [], []
+    for r in range(n):
+        near = np.arange(8 * (r // 8), 8 * (r // 8) + 8)   # the whole block, then random columns
+        rest = np.setdiff1d(rng.permutation(n)[:lengths[r // 64]], near)[:lengths[r // 64] - 8]
+        c = np.concatenate([near, rest])
+        rows += [r] * len(c)
+        cols += c.tolist()
+        vals += (rng.uniform(-1, 1, len(c)) / len(c) + 4.0 * (c == r)).tolist()
+    A = sp.csr_matrix((vals, (rows, cols)), shape=(n, n))
+    P = sp.csr_matrix((np.ones(n), (np.arange(n), np.arange(n) // 8)), shape=(n, n // 8))
+    levels = [Level(A, 8, P, 0.125), Level(sp.csr_matrix(0.125 * (P.T @ A @ P)), 1, None)]
+    s = gpu_lib.Solver(levels)
+    s.setup(depth=1, precision=precision)
+    lam = [rng.uniform(-1, 1, size=(n // 8, 8, 8)) / 16 for _ in range(1)]
+    s.set_smoother(0, 1, lam[0])
+    b, x = rng.uniform(-1, 1, size=(n, nrhs)), rng.uniform(-1, 1, size=(n, nrhs))
+    ref = O.smooth(A, dict(lam=lam), x, b)
+    # 70 products of order 1 in 2^-53 or 2^-24: 1e-14 and 1e-5 with room
+    tol = 1e-13 if precision == "fp64" else 1e-5
+    check_vec(s.smooth(0, b, x).cpu().numpy(), ref, tol, f"long rows {precision} nrhs={nrhs}")
