@@ -976,20 +976,48 @@ __global__ __launch_bounds__(WG) void k_cg_zq_flat(int64_t npairs, int nsys, con
     flat_partials<R>(v, red, partial);
 }
 
-// p = z + beta p (first: p = z), beta = -(z, q_prev) / (p_prev, q_prev)
+// Sums of partials[n / W][W] for every workgroup that needs them, in the order of
+// k_reduce_partials (N = 1024 accumulators) or k_wg_to_sys (256): the same bits,
+// without a launch of 3 to 4 us between the kernel that leaves the partials and
+// the one that uses them.  The sums in red[0, W), after a barrier.
+template <int N, int W>
+__device__ __forceinline__ void fold_partials(const double *__restrict__ partial, int64_t n, double *red) {
+#pragma unroll
+    for (int j = 0; j < N / WG; ++j) {
+        const int vt = threadIdx.x + j * WG;
+        double s = 0.0;
+        for (int64_t e = vt; e < n; e += N) s += partial[e];
+        red[vt] = s;
+    }
+    __syncthreads();
+    for (int h = N / 2; h >= W; h >>= 1) {
+        for (int vt = threadIdx.x; vt < h; vt += WG) red[vt] += red[vt + h];
+        __syncthreads();
+    }
+}
+
+// p = z + beta p (first: p = z), beta = -(z, q_prev) / (p_prev, q_prev), (z, q_prev)
+// from the partials of k_cg_zq_flat
 template <typename T, int R>
 __global__ __launch_bounds__(WG) void k_cg_p_flat(int64_t npairs, int nsys, const int32_t *__restrict__ sys_wg,
                                                   const int64_t *__restrict__ sys_ptr, const T *__restrict__ z,
-                                                  const double *__restrict__ zq, const double *__restrict__ pq_prev,
-                                                  double *__restrict__ p, int first) {
+                                                  const double *__restrict__ zq_part,
+                                                  const double *__restrict__ pq_prev, double *__restrict__ p,
+                                                  int first) {
+    __shared__ double zq[1024];
     const PairRange pr = pair_range<R>(npairs, nsys, sys_wg, sys_ptr);
     double beta[2] = {0.0, 0.0};
     if (!first) {
+        if (sys_wg)
+            fold_partials<256, R>(zq_part + (int64_t)sys_wg[pr.sys] * R,
+                                  (int64_t)(sys_wg[pr.sys + 1] - sys_wg[pr.sys]) * R, zq);
+        else
+            fold_partials<1024, R>(zq_part, (int64_t)gridDim.x * R, zq);
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int k = (int)((2 * pr.begin + u) % R);
             const double d = pq_prev[pr.sys * 2 * R + k];
-            beta[u] = d > 0.0 ? -zq[pr.sys * R + k] / d : 0.0;
+            beta[u] = d > 0.0 ? -zq[k] / d : 0.0;
             if (!isfinite(beta[u])) beta[u] = 0.0;
         }
     }
@@ -1004,22 +1032,30 @@ __global__ __launch_bounds__(WG) void k_cg_p_flat(int64_t npairs, int nsys, cons
     }
 }
 
-// x += alpha p, r -= alpha q, rt = r (working precision), partial r^2
+// x += alpha p, r -= alpha q, rt = r (working precision), partial r^2.  One
+// system: (p, q) and (p, r) from the n_part partials of k_cg_ap, kept in pq
+// for the next direction; a batch: from pq.
 template <typename T, int R>
 __global__ __launch_bounds__(WG) void k_cg_update_flat(int64_t npairs, int nsys, const int32_t *__restrict__ sys_wg,
                                                        const int64_t *__restrict__ sys_ptr,
-                                                       const double *__restrict__ pq, const double *__restrict__ p,
+                                                       double *pq, const double *__restrict__ pq_part,
+                                                       int64_t n_part, const double *__restrict__ p,
                                                        const double *__restrict__ q, double *__restrict__ x,
                                                        double *__restrict__ r, T *__restrict__ rt,
                                                        double *__restrict__ partial) {
-    __shared__ double red[2 * WG];
+    __shared__ double red[1024];
     const PairRange pr = pair_range<R>(npairs, nsys, sys_wg, sys_ptr);
     double alpha[2];
+    const double *dots = pq + pr.sys * 2 * R;
+    if (!sys_wg) {
+        fold_partials<1024, 2 * R>(pq_part, n_part * 2 * R, red);
+        if (blockIdx.x == 0 && threadIdx.x < 2 * R) pq[threadIdx.x] = red[threadIdx.x];
+    }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int k = (int)((2 * pr.begin + u) % R);
-        const double d = pq[pr.sys * 2 * R + k];
-        alpha[u] = d > 0.0 ? pq[pr.sys * 2 * R + R + k] / d : 0.0;
+        const double d = sys_wg ? dots[k] : red[k], n = sys_wg ? dots[R + k] : red[R + k];
+        alpha[u] = d > 0.0 ? n / d : 0.0;
         if (!isfinite(alpha[u])) alpha[u] = 0.0;
     }
     double v[2] = {0.0, 0.0};
@@ -1041,6 +1077,7 @@ __global__ __launch_bounds__(WG) void k_cg_update_flat(int64_t npairs, int nsys,
         vstore<double, 2>(r + 2 * e2, rr);
         vstore<T, 2>(rt + 2 * e2, o);
     }
+    __syncthreads();   // red has been read
     flat_partials<R>(v, red, partial);
 }
 
@@ -1223,7 +1260,7 @@ __global__ __launch_bounds__(WG) void k_gm_xupdate(int64_t nel, int nsys, const 
 // sc = 1 / sqrt(sum) (0 for a zero or non-finite sum).
 __global__ __launch_bounds__(1024) void k_gm_reduce(int W, int WP, int64_t G, const int32_t *__restrict__ sys_wg,
                                                     const double *__restrict__ partial, double *__restrict__ out,
-                                                    double *__restrict__ sc) {
+                                                    double *__restrict__ sc, double *__restrict__ host) {
     __shared__ double red[16][64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int s = blockIdx.y;
@@ -1250,6 +1287,7 @@ __global__ __launch_bounds__(1024) void k_gm_reduce(int W, int WP, int64_t G, co
 #pragma unroll
         for (int w = 0; w < 16; ++w) t += red[w][lane];
         out[(int64_t)s * W + c] = t;
+        host[(int64_t)s * W + c] = t;
         if (sc) sc[(int64_t)s * W + c] = (t > 0.0 && isfinite(t)) ? 1.0 / sqrt(t) : 0.0;
     }
 }
@@ -1303,10 +1341,13 @@ __global__ __launch_bounds__(WG) void k_gm_scale_cast(int64_t nel, int nsys, con
     for (int64_t e = er.begin; e < er.end; e += er.stride) out[e] = (T)(f * vt[e]);
 }
 
+// The sums that the host tests go to its pinned copy (host, may be null) from the
+// reduction itself: a copy behind it was one more launch of 4 us per iteration.
 // Per-system sums of per-workgroup partials: out[s][k] = sum over the
 // workgroups b of system s (sys_wg[s] <= b < sys_wg[s+1]) of partial[b][k].
 __global__ __launch_bounds__(256) void k_wg_to_sys(int W, const int32_t *__restrict__ sys_wg,
-                                                   const double *__restrict__ partial, double *__restrict__ out) {
+                                                   const double *__restrict__ partial, double *__restrict__ out,
+                                                   double *__restrict__ host) {
     __shared__ double red[256];
     const int t = threadIdx.x;
     const int64_t e0 = (int64_t)sys_wg[blockIdx.x] * W, e1 = (int64_t)sys_wg[blockIdx.x + 1] * W;
@@ -1318,14 +1359,17 @@ __global__ __launch_bounds__(256) void k_wg_to_sys(int W, const int32_t *__restr
         if (t < h) red[t] += red[t + h];
         __syncthreads();
     }
-    if (t < W) out[(int64_t)blockIdx.x * W + t] = red[t];
+    if (t < W) {
+        out[(int64_t)blockIdx.x * W + t] = red[t];
+        if (host) host[(int64_t)blockIdx.x * W + t] = red[t];
+    }
 }
 
 // Fixed-order sum of the partials: out[k] = sum_g partial[g][k]
 // One coalesced pass: thread t always accumulates component t % R (R divides
 // 1024), then a tree over threads of equal t % R.
 __global__ __launch_bounds__(1024) void k_reduce_partials(int64_t G, int R, const double *__restrict__ partial,
-                                                          double *__restrict__ out) {
+                                                          double *__restrict__ out, double *__restrict__ host) {
     __shared__ double red[1024];
     const int t = threadIdx.x;
     double s = 0.0;
@@ -1336,7 +1380,10 @@ __global__ __launch_bounds__(1024) void k_reduce_partials(int64_t G, int R, cons
         if (t < h) red[t] += red[t + h];
         __syncthreads();
     }
-    if (t < R) out[t] = red[t];
+    if (t < R) {
+        out[t] = red[t];
+        if (host) host[t] = red[t];
+    }
 }
 
 // Per-system squared norms from the slice sums of k_ir_residual<SYS>:
@@ -1347,7 +1394,8 @@ __global__ __launch_bounds__(1024) void k_reduce_partials(int64_t G, int R, cons
 __global__ __launch_bounds__(256) void k_sys_norms(int R, int64_t n, const int64_t *__restrict__ sys_ptr,
                                                    const int32_t *__restrict__ het,
                                                    const double *__restrict__ spart,
-                                                   const double *__restrict__ rn2, double *__restrict__ out) {
+                                                   const double *__restrict__ rn2, double *__restrict__ out,
+                                                   double *__restrict__ host) {
     __shared__ double red[256];
     const int t = threadIdx.x;
     const int64_t r0 = sys_ptr[blockIdx.x], r1 = sys_ptr[blockIdx.x + 1];
@@ -1377,7 +1425,10 @@ __global__ __launch_bounds__(256) void k_sys_norms(int R, int64_t n, const int64
         if (t < h) red[t] += red[t + h];
         __syncthreads();
     }
-    if (t < R) out[(int64_t)blockIdx.x * R + t] = red[t];
+    if (t < R) {
+        out[(int64_t)blockIdx.x * R + t] = red[t];
+        if (host) host[(int64_t)blockIdx.x * R + t] = red[t];
+    }
 }
 
 template <typename T>
@@ -1897,7 +1948,7 @@ void ensure_workspace(Ctx &c, int nrhs) {
     c.ws_scratch = true;   // forces the pointer update below
     use_own_workspace(c);
     const int64_t G = std::min<int64_t>(ceil_div(c.lv[0].sell.nslices, 4), IR_GRID);
-    c.ir_partial.alloc(std::max<int64_t>(G, 1) * 2 * nrhs);   // up to two dot products per RHS
+    c.ir_partial.alloc(std::max<int64_t>(G, 1) * 3 * nrhs);   // up to two dot products per RHS, and one beside them
     const int64_t nsys = c.sys_ptr.empty() ? 1 : (int64_t)c.sys_ptr.size() - 1;
     c.ir_norm.alloc(2 * nsys * nrhs);
     if (nsys > 1) {
@@ -2383,6 +2434,7 @@ void solve_ir(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
             const double up_bytes = (double)L0.n * R * (16.0 + sizeof(T));
             // squared norms of r (and of b, at offset nsys*R): per system in a batch
             const bool batch = nsys > 1;
+            auto host = [&](double *out) { return c.h_norm + (out - c.ir_norm.get()); };
             auto norms = [&](const double *xx, T *rt, double *out) {
                 if (batch) {
                     dispatch_nb((int)L0.nb, [&](auto nbc) {
@@ -2392,7 +2444,7 @@ void solve_ir(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                                            xx, rt, (double *)nullptr, c.sys_het.get(), c.sys_spart.get(), c.rn2.get());
                     });
                     hipLaunchKernelGGL(k_sys_norms, dim3(nsys), dim3(256), 0, c.stream, R, S.nrows,
-                                       c.sys_ptr_d.get(), c.sys_het.get(), c.sys_spart.get(), c.rn2.get(), out);
+                                       c.sys_ptr_d.get(), c.sys_het.get(), c.sys_spart.get(), c.rn2.get(), out, host(out));
                 } else {
                     dispatch_nb((int)L0.nb, [&](auto nbc) {
                         constexpr int NB = decltype(nbc)::value;
@@ -2402,7 +2454,7 @@ void solve_ir(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                                            (double *)nullptr);
                     });
                     hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(1024), 0, c.stream, G, R, c.ir_partial.get(),
-                                       out);
+                                       out, host(out));
                 }
                 CS_LAUNCH_CHECK();
             };
@@ -2446,9 +2498,7 @@ void solve_ir(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
             SpecReset spec_reset{c};
             const Ctx::GraphKey key{b, x, R, c.precision, 0, c.gen, 0};
             for (;; ++it) {
-                CS_HIP(hipMemcpyAsync(c.h_norm, c.ir_norm.get(), 2 * nsys * R * sizeof(double),
-                                      hipMemcpyDeviceToHost, c.stream));
-                CS_HIP(hipEventRecord(c.ev_norm, c.stream));
+                CS_HIP(hipEventRecord(c.ev_norm, c.stream));   // h_norm is written by the reduction
                 // the next V-cycle's first sweep reads only r and Lambda: issued
                 // while the host waits for the norms (one wasted sweep when this
                 // check ends the solve)
@@ -2486,7 +2536,6 @@ void solve_ir(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
 // iteration for the stopping test.
 void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int maxit, cs_info *info,
               double *history, cs_status *st) {
-    ensure_workspace(c, nrhs);
     Level &L0 = c.lv[0];
     const Sell &S = L0.sell;
     const int64_t n = L0.n * nrhs;
@@ -2494,7 +2543,8 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
     const int nsys = c.sys_ptr.empty() ? 1 : (int)c.sys_ptr.size() - 1;
     const bool batch = nsys > 1;
     // grown only: a release would synchronise the device (the pool waits as
-    // hipFree does); a new buffer makes a captured iteration stale
+    // hipFree does); a new buffer makes a captured iteration stale, and the tail's
+    // table with it, which ensure_workspace then builds again
     if (c.cg_r.n < (size_t)n) {
         c.cg_r.alloc(n);
         c.cg_p.alloc(n);
@@ -2506,6 +2556,7 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
         c.cg_pq.alloc((size_t)nsys * 2 * nrhs);
         c.gen++;
     }
+    ensure_workspace(c, nrhs);
     double *r = c.cg_r.get(), *p = c.cg_p.get(), *q = c.cg_q.get();
     *st = CS_OK;
     const bool graphs = c.use_graphs && !c.tr.on;
@@ -2518,13 +2569,14 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
             T *rt = reinterpret_cast<T *>(L0.w_bb);
             const T *z = reinterpret_cast<const T *>(L0.w_xb);
             // reduce partial sums of W values per row into out[nsys][W]
-            auto reduce = [&](int W, double *out) {
+            auto reduce = [&](int W, double *out, double *host = nullptr) {
                 if (batch)
                     hipLaunchKernelGGL(k_sys_norms, dim3(nsys), dim3(256), 0, c.stream, W, S.nrows,
-                                       c.sys_ptr_d.get(), c.sys_het.get(), c.sys_spart.get(), c.rn2.get(), out);
+                                       c.sys_ptr_d.get(), c.sys_het.get(), c.sys_spart.get(), c.rn2.get(), out,
+                                       host);
                 else
                     hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(1024), 0, c.stream, G, W, c.ir_partial.get(),
-                                       out);
+                                       out, host);
                 CS_LAUNCH_CHECK();
             };
             const double vec = (double)L0.n * R * 8.0;
@@ -2543,12 +2595,13 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                 sys_wg = c.cg_sys_wg.get();
                 if (c.cg_partial.n < (size_t)(Gf * R)) c.cg_partial.alloc(Gf * R);
             }
-            double *fpart = sys_wg ? c.cg_partial.get() : c.ir_partial.get();
-            auto reduce_flat = [&](double *out) {   // flat-kernel partials [Gf][R] -> out[nsys][R]
+            // behind the [G][2R] partials of k_cg_ap, which the update reads as it writes its own
+            double *fpart = sys_wg ? c.cg_partial.get() : c.ir_partial.get() + G * 2 * R;
+            auto reduce_flat = [&](double *out, double *host) {   // flat-kernel partials [Gf][R] -> out[nsys][R]
                 if (sys_wg)
-                    hipLaunchKernelGGL(k_wg_to_sys, dim3(nsys), dim3(256), 0, c.stream, R, sys_wg, fpart, out);
+                    hipLaunchKernelGGL(k_wg_to_sys, dim3(nsys), dim3(256), 0, c.stream, R, sys_wg, fpart, out, host);
                 else
-                    hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(1024), 0, c.stream, Gf, R, fpart, out);
+                    hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(1024), 0, c.stream, Gf, R, fpart, out, host);
                 CS_LAUNCH_CHECK();
             };
             // ||b||^2 and rt = b; r = b; x = 0
@@ -2562,9 +2615,8 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                                    c.ir_partial.get(), (const int32_t *)nullptr, (double *)nullptr,
                                    (double *)nullptr);
             CS_LAUNCH_CHECK();
-            reduce(R, c.ir_norm.get() + nsys * R);
-            CS_HIP(hipMemcpyAsync(c.ir_norm.get(), c.ir_norm.get() + nsys * R, nsys * R * sizeof(double),
-                                  hipMemcpyDeviceToDevice, c.stream));
+            reduce(R, c.ir_norm.get() + nsys * R, c.h_norm + nsys * R);
+            reduce(R, c.ir_norm.get(), c.h_norm);
             CS_HIP(hipMemcpyAsync(r, b, n * sizeof(double), hipMemcpyDeviceToDevice, c.stream));
             hipLaunchKernelGGL(k_zero<double>, dim3(grid_for(n)), dim3(WG), 0, c.stream, n, x);
             CS_LAUNCH_CHECK();
@@ -2584,7 +2636,6 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                         hipLaunchKernelGGL((k_cg_zq_flat<T, R>), dim3(Gf), dim3(WG), 0, c.stream, npairs, nsys, sys_wg,
                                            c.sys_ptr_d.get(), z, q, fpart);
                         CS_LAUNCH_CHECK();
-                        reduce_flat(c.cg_zq.get());
                     } else {
                         if (batch)
                             hipLaunchKernelGGL((k_cg_zq<T, R, true>), dim3(G), dim3(WG), 0, c.stream, S.nrows,
@@ -2603,7 +2654,7 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                                        c.sys_ptr_d.get(), z, c.cg_zq.get(), pq, p, first ? 1 : 0);
                 else
                     hipLaunchKernelGGL((k_cg_p_flat<T, R>), dim3(Gf), dim3(WG), 0, c.stream, npairs, nsys, sys_wg,
-                                       c.sys_ptr_d.get(), z, c.cg_zq.get(), pq, p, first ? 1 : 0);
+                                       c.sys_ptr_d.get(), z, fpart, pq, p, first ? 1 : 0);
                 CS_LAUNCH_CHECK();
                 trace_end(c, slot);
                 slot = trace_begin(c, CS_TRACE_REFINE, S.nnz * 12.0 + 3.0 * vec);
@@ -2623,14 +2674,14 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                                            c.ir_partial.get());
                     });
                 CS_LAUNCH_CHECK();
-                reduce(2 * R, pq);
+                if (batch || !flat) reduce(2 * R, pq);
                 trace_end(c, slot);
                 slot = trace_begin(c, CS_TRACE_REFINE, 6.0 * vec + L0.n * R * sizeof(T));
                 if (flat) {
                     hipLaunchKernelGGL((k_cg_update_flat<T, R>), dim3(Gf), dim3(WG), 0, c.stream, npairs, nsys, sys_wg,
-                                       c.sys_ptr_d.get(), pq, p, q, x, r, rt, fpart);
+                                       c.sys_ptr_d.get(), pq, c.ir_partial.get(), G, p, q, x, r, rt, fpart);
                     CS_LAUNCH_CHECK();
-                    reduce_flat(c.ir_norm.get());
+                    reduce_flat(c.ir_norm.get(), c.h_norm);
                 } else {
                     if (batch)
                         hipLaunchKernelGGL((k_cg_update<T, R, true>), dim3(G), dim3(WG), 0, c.stream, S.nrows,
@@ -2642,15 +2693,13 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                                            (const int32_t *)nullptr, (double *)nullptr, (double *)nullptr,
                                            c.ir_partial.get());
                     CS_LAUNCH_CHECK();
-                    reduce(R, c.ir_norm.get());
+                    reduce(R, c.ir_norm.get(), c.h_norm);
                 }
                 trace_end(c, slot);
             };
             const Ctx::GraphKey key{b, x, R, c.precision, 0, c.gen, 1};
             for (;; ++it) {
-                CS_HIP(hipMemcpyAsync(c.h_norm, c.ir_norm.get(), 2 * nsys * R * sizeof(double),
-                                      hipMemcpyDeviceToHost, c.stream));
-                CS_HIP(hipEventRecord(c.ev_norm, c.stream));
+                CS_HIP(hipEventRecord(c.ev_norm, c.stream));   // h_norm is written by the reduction
                 if (it < maxit) issue_first_sweep<T, R>(c);   // wasted (one sweep) when this check ends the solve
                 CS_HIP(hipEventSynchronize(c.ev_norm));
                 const double rel = mon.record(it, c.h_norm);
@@ -2752,7 +2801,7 @@ void solve_gmres(Ctx &c, const double *b, double *x, int nrhs, double rtol, int 
                 int WP = 1;
                 while (WP < W && WP < 64) WP *= 2;
                 hipLaunchKernelGGL(k_gm_reduce, dim3((unsigned)ceil_div(W, 64), (unsigned)nsys), dim3(1024), 0,
-                                   c.stream, W, WP, Gp, sys_wg, part, out, rsqrt_out);
+                                   c.stream, W, WP, Gp, sys_wg, part, out, rsqrt_out, c.gm_host + (out - dh));
                 CS_LAUNCH_CHECK();
             };
             const dim3 gg((unsigned)Gp);
@@ -2788,7 +2837,6 @@ void solve_gmres(Ctx &c, const double *b, double *x, int nrhs, double rtol, int 
                 }
                 CS_LAUNCH_CHECK();
                 reduce(R, n2, sc);
-                CS_HIP(hipMemcpyAsync(c.gm_host, n2, ncol * sizeof(double), hipMemcpyDeviceToHost, c.stream));
                 CS_HIP(hipStreamSynchronize(c.stream));
             };
             hipLaunchKernelGGL(k_zero<double>, dim3(grid_for(nel)), dim3(WG), 0, c.stream, nel, x);
@@ -2902,8 +2950,6 @@ void solve_gmres(Ctx &c, const double *b, double *x, int nrhs, double rtol, int 
                     });
                     CS_LAUNCH_CHECK();
                     reduce(R, n2, sc + (int64_t)(j + 1) * ncol);
-                    CS_HIP(hipMemcpyAsync(c.gm_host, dh, (size_t)(2 * nv + 1) * ncol * sizeof(double),
-                                          hipMemcpyDeviceToHost, c.stream));
                     CS_HIP(hipStreamSynchronize(c.stream));
                     trace_end(c, slot);
                     ++it;

@@ -226,3 +226,28 @@ def test_gmres_sizes_and_basis_lengths(gpu_lib, n, nrhs, flexible):
     assert info["iterations"] == len(ho) - 1
     np.testing.assert_allclose(info["history"], ho, rtol=1e-6, atol=1e-13)
     check_vec(x.cpu().numpy(), xo, 1e-8, f"GMRES {n}x{nrhs} flexible={flexible} iterate vs oracle")
+
+
+# workgroups of the dot products: 1, 2 (a row past one workgroup's), 16, 256, 1024;
+# odd lengths take the row-wise kernels
+@pytest.mark.parametrize("n,nrhs", [(8, 1), (8, 8), (18, 1), (18, 2), (27, 1), (64, 4), (256, 2), (256, 8), (512, 1)])
+def test_cg_sizes_and_first_solve(gpu_lib, n, nrhs):
+    """CG over the grid sizes of its dot products against the oracle's FCG around
+    the same V-cycle (a depth-1 cascade), the tail V-cycle on in the solver's
+    first solve; a second solve repeats its bits, graph replay too."""
+    p = fd.lognormal2d(n, 1.0, nrhs) if n % 2 else fd.poisson2d(n, nrhs=nrhs)
+    s = gpu_lib.Solver(p.levels)
+    s.setup(depth=1, n_pre=1, n_post=1)
+    pre = lambda r: s.vcycle(r).cpu().numpy()
+    xo, ho = O.fcg(p.levels[0].A, pre, p.rhs, rtol=1e-9, maxit=12)
+    s.set_tail(4096)
+    kw = dict(rtol=1e-9, maxit=12, method="cg", raise_on_noconv=False)
+    x, info = s.solve(p.rhs, **kw)
+    assert info["iterations"] == len(ho) - 1
+    np.testing.assert_allclose(info["history"], ho, rtol=1e-6, atol=1e-13)   # one level: rounding
+    check_vec(x.cpu().numpy(), xo, 1e-8, f"FCG {n}x{nrhs} iterate vs oracle")
+    for graphs in (False, True):
+        s.set_graphs(graphs)
+        x2, i2 = s.solve(p.rhs, **kw)
+        np.testing.assert_array_equal(x2.cpu().numpy(), x.cpu().numpy())
+        np.testing.assert_array_equal(i2["history"], info["history"])
