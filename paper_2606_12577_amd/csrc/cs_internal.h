@@ -399,13 +399,13 @@ void tail_prepare(Ctx &c, int nrhs);
 inline bool tail_covers(const Ctx &c, int l, int nrhs) {
     return l == c.tail_from && c.tail_gen == c.gen && c.tail_prec == c.precision && c.tail_nrhs == nrhs;
 }
-void tail_launch(Ctx &c, int nrhs, const double *b64 = nullptr, double *x64 = nullptr);
+void tail_launch(Ctx &c, int nrhs, const double *b64 = nullptr, double *x64 = nullptr, bool add = false);
 int tail16_rounds(const Level &L);
 int64_t tail16_schedule_words(const Level &L);
 void tail16_schedule(const Level &L, uint32_t zero, std::vector<int32_t> &out);
 int64_t tail16_pack(Ctx &c, const Level &L, unsigned short *out);
 void tail16_prepare(Ctx &c);
-void tail16_launch(Ctx &c, hipEvent_t ev0, hipEvent_t ev1, const double *b64, double *x64);
+void tail16_launch(Ctx &c, hipEvent_t ev0, hipEvent_t ev1, const double *b64, double *x64, bool add);
 
 // solve.hip
 int tune_tail(Ctx &c, int nrhs, int64_t *rows, double *ms, int cap);

@@ -1820,7 +1820,9 @@ bool issue_first_sweep(Ctx &c) {
 template <typename T, int R>
 void vcycle_level(Ctx &c, int l) {
     if (tail_covers(c, l, R)) {
-        tail_launch(c, R);
+        const bool add = l == 0 && c.acc_x64;   // the refinement's x += x_0 in the same launch
+        tail_launch(c, R, nullptr, add ? c.acc_x64 : nullptr, add);
+        c.acc_done = c.acc_done || add;
         return;
     }
     Level &L = c.lv[l];
@@ -2469,12 +2471,13 @@ void solve_ir(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                 // (128^3, 8 RHS: 52.2 -> 49.9 ms); in FP32 the accumulating
                 // sweep holds more registers than the plain one (three waves per
                 // SIMD instead of four) and the solve gained nothing (24.35 vs
-                // 24.39 ms), so FP32 keeps the separate pass
+                // 24.39 ms), so FP32 keeps the separate pass; a V-cycle that is one
+                // tail launch adds d in either precision
                 struct AccScope {
                     Ctx &c;
                     ~AccScope() { c.acc_x64 = nullptr; }   // also when a launch fails
                 } scope{c};
-                c.acc_x64 = std::is_same<T, double>::value ? x : nullptr;
+                c.acc_x64 = std::is_same<T, double>::value || tail_covers(c, 0, R) ? x : nullptr;
                 c.acc_done = false;
                 vcycle_level<T, R>(c, 0);
                 c.acc_x64 = nullptr;

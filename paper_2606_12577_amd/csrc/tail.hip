@@ -238,7 +238,7 @@ template <typename T, int NB>
 __global__ __launch_bounds__(TAIL_WG) void k_tail_vcycle(const TailLevel *__restrict__ tab, int nlev, int nsys,
                                                          const int32_t *__restrict__ sys, int R, int n_pre,
                                                          int n_post, int rf, int alt_off,
-                                                         const double *__restrict__ b64, double *__restrict__ x64) {
+                                                         const double *__restrict__ b64, double *x64, int add) {
     extern __shared__ __align__(16) unsigned char tail_lds[];
     T *const base = reinterpret_cast<T *>(tail_lds);
     T *const alt = base + alt_off;
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(TAIL_WG) void k_tail_vcycle(const TailLevel *__rest
     auto gx = (__attribute__((address_space(1))) T *)static_cast<T *>(tab[0].xb);
     for (int r = threadIdx.x; r < m; r += TAIL_WG) {
         const int64_t e = (int64_t)(lo + r) * R + k;
-        if (x64) x64[e] = (double)x[r];
+        if (x64) x64[e] = add ? x64[e] + (double)x[r] : (double)x[r];
         else gx[e] = x[r];
     }
 }
@@ -577,11 +577,11 @@ void tail_table(Ctx &c, int nrhs) {
 }
 
 template <typename T>
-void launch(Ctx &c, int nrhs, const double *b64, double *x64) {
+void launch(Ctx &c, int nrhs, const double *b64, double *x64, bool add) {
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     (void)trace_begin_launch(c, CS_TRACE_TAIL, c.tail_bytes, &ev0, &ev1);
     if (c.tail_b16) {
-        tail16_launch(c, ev0, ev1, b64, x64);
+        tail16_launch(c, ev0, ev1, b64, x64, add);
         return;
     }
     // workgroups that warm the L2 where the cycle's own few come after other levels
@@ -591,7 +591,7 @@ void launch(Ctx &c, int nrhs, const double *b64, double *x64) {
         hipExtLaunchKernelGGL((k_tail_vcycle<T, NB>), dim3(n <= 8 && c.tail_from > 0 ? 8 * (1 + TAIL_HELPERS) : n), dim3(TAIL_WG), (unsigned)c.tail_lds,
                               c.stream, ev0, ev1, 0, (const TailLevel *)c.tail_tab.get(),
                               (int)c.lv.size() - c.tail_from, c.tail_nsys, (const int32_t *)c.tail_sys.get(), nrhs,
-                              c.opt.n_pre, c.opt.n_post, c.opt.order == CS_RF ? 1 : 0, c.tail_alt, b64, x64);
+                              c.opt.n_pre, c.opt.n_post, c.opt.order == CS_RF ? 1 : 0, c.tail_alt, b64, x64, add ? 1 : 0);
     });
     CS_LAUNCH_CHECK();
 }
@@ -606,10 +606,11 @@ void tail_prepare(Ctx &c, int nrhs) {
 }
 
 // The V-cycle from level c.tail_from down, in one launch; with b64 and x64 from
-// and into those FP64 vectors instead of the level's workspace.
-void tail_launch(Ctx &c, int nrhs, const double *b64, double *x64) {
-    if (c.precision == CS_FP64) launch<double>(c, nrhs, b64, x64);
-    else launch<float>(c, nrhs, b64, x64);
+// and into those FP64 vectors instead of the level's workspace; with `add` the
+// result is added to x64.
+void tail_launch(Ctx &c, int nrhs, const double *b64, double *x64, bool add) {
+    if (c.precision == CS_FP64) launch<double>(c, nrhs, b64, x64, add);
+    else launch<float>(c, nrhs, b64, x64, add);
 }
 
 }  // namespace cs

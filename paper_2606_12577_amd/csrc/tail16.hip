@@ -213,7 +213,7 @@ __global__ __launch_bounds__(TAIL_WG) void k_tail_bsr16(const TailLevel *__restr
                                                         const int32_t *__restrict__ rows, int n_pre, int n_post,
                                                         int rf, int alt_off, int zero_off,
                                                         const int32_t *__restrict__ sched, int sched_words, const double *__restrict__ b64,
-                                                        double *__restrict__ x64) {
+                                                        double *x64, int add) {
     extern __shared__ __align__(16) unsigned char tail16_lds[];
     if (blockIdx.x) {
         tail_warm(tab, nlev, 1);
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(TAIL_WG) void k_tail_bsr16(const TailLevel *__restr
     }
     auto gx = (__attribute__((address_space(1))) float *)static_cast<float *>(tab[0].xb);
     for (int r = t; r < m; r += TAIL_WG) {
-        if (x64) x64[r] = (double)x[r];
+        if (x64) x64[r] = add ? x64[r] + (double)x[r] : (double)x[r];
         else gx[r] = x[r];
     }
 }
@@ -343,12 +343,12 @@ void tail16_prepare(Ctx &c) {
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.tail_lds));
 }
 
-void tail16_launch(Ctx &c, hipEvent_t ev0, hipEvent_t ev1, const double *b64, double *x64) {
+void tail16_launch(Ctx &c, hipEvent_t ev0, hipEvent_t ev1, const double *b64, double *x64, bool add) {
     hipExtLaunchKernelGGL(k_tail_bsr16, dim3(8 * (1 + TAIL_HELPERS)), dim3(TAIL_WG), (unsigned)c.tail_lds, c.stream, ev0, ev1, 0,
                           (const TailLevel *)c.tail_tab.get(), (int)c.lv.size() - c.tail_from,
                           (const int32_t *)c.tail_sys.get(), c.opt.n_pre, c.opt.n_post, c.opt.order == CS_RF ? 1 : 0,
                           c.tail_alt, c.tail_zero, (const int32_t *)c.tail_sched.get(),
-                          (int)c.tail_sched_host.size(), b64, x64);
+                          (int)c.tail_sched_host.size(), b64, x64, add ? 1 : 0);
     CS_LAUNCH_CHECK();
 }
 
