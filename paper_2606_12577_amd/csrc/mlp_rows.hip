@@ -157,9 +157,15 @@ __global__ __launch_bounds__(RW) void k_rows(RowArgs a) {
         return B;
     };
     f32x4 acc[RT];
-    auto product = [&](const Frag &B) {   // acc = At B
+    // acc = At B; small tiles (batches) in four sums of 32 products each, which
+    // rounds half as much as one chain of 128
+    constexpr int NS = RT == 1 ? 4 : 1;
+    auto product = [&](const Frag &B) {
+        f32x4 part[NS][RT];
 #pragma unroll
-        for (int i = 0; i < RT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int p = 0; p < NS; ++p)
+#pragma unroll
+            for (int i = 0; i < RT; ++i) part[p][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) {
             f32x4 av[RT];
@@ -168,7 +174,12 @@ __global__ __launch_bounds__(RW) void k_rows(RowArgs a) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int i = 0; i < RT; ++i) acc[i] = mfma(av[i][j], B.k[kk][j], acc[i]);
+                for (int i = 0; i < RT; ++i) part[kk % NS][i] = mfma(av[i][j], B.k[kk][j], part[kk % NS][i]);
+        }
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            if constexpr (NS == 4) acc[i] = (part[0][i] + part[1][i]) + (part[2][i] + part[3][i]);
+            else acc[i] = part[0][i];
         }
     };
     // every element of the tile: f(i, r, tile row, global row)
@@ -397,16 +408,16 @@ __device__ __forceinline__ float grad_sum(const SumArgs &s, int64_t e) {
             slot = l;
             c = e - s.off[2 * l + 1];
         }
-    float v = 0.f;
+    double v = 0.0;   // rounded once
     if (slot >= 0) {
         const float *p = s.bpart + slot * NP + c;
 #pragma unroll 8
-        for (int b = 0; b < s.G; ++b) v += p[(int64_t)b * 3 * NP];
+        for (int b = 0; b < s.G; ++b) v += (double)p[(int64_t)b * 3 * NP];
     } else {
 #pragma unroll 4
-        for (int z = 0; z < s.SW; ++z) v += s.wpart[z * s.np + e];
+        for (int z = 0; z < s.SW; ++z) v += (double)s.wpart[z * s.np + e];
     }
-    return v;
+    return (float)v;
 }
 
 __global__ __launch_bounds__(WG) void k_grad_rows(SumArgs s, float *__restrict__ g) {
