@@ -471,7 +471,7 @@ class Solver:
 
     def set_tail(self, max_rows: int):
         """Run the V-cycle on the coarse levels of at most max_rows rows as one
-        single-workgroup launch (0: per-level launches)."""
+        launch, a workgroup per system and right-hand side (0: per-level launches)."""
         self._check(self._lib.cs_set_tail(self._h, int(max_rows)))
 
     def tail(self):

@@ -23,12 +23,12 @@ namespace {
 // batch do not see each other, so they go to different CUs.  Every row's
 // arithmetic is the per-level kernels' own, in the same order: identical
 // results.
-// What bounds it is one CU: about 0.5-1 us per sweep up to 1024 point rows and
-// 2 us at 4096 (a per-level launch takes 3.5-4 us), but 6 us for 2048 rows of
-// 8x8 blocks (110 KB of Lambda per sweep and system), so cs_autotune picks the
+// What bounds it is one CU: about 0.4 us per sweep up to 1024 point rows and 2 us
+// at 4096 (a per-level launch takes 3.5-4 us), but as much as a launch for 1728
+// rows of 8x8 FP64 blocks (110 KB of Lambda per sweep), so cs_autotune picks the
 // first level by timing.  One V(2,2) of the 64^2 FP64 problem: 142 us with a
 // launch per step, 93 us in the form with all vectors in the L2 and one
-// workgroup for all right-hand sides and systems, 51 us now; V-cycle of 16
+// workgroup for all right-hand sides and systems, 49 us now; V-cycle of 16
 // systems of 64^2 to 176^2 with 4 right-hand sides: 118 us per level, 82 now.
 // Behind large levels (96^3 FP64, from 1728 rows of 8x8 blocks on) the workgroups
 // of tail_warm are worth 18 us of a 375 us V-cycle.
