@@ -199,7 +199,7 @@ __device__ void normal_solve(const double *G, const double *H, double *Lc, doubl
 
 // Fused fit step of a level of 8x8 blocks (fit8.hip): per list row M_i = sum_j
 // A~_ij E_j, the normal equations, Lambda~_i and, with nval, the updated row of
-// E on pattern(M_i).
+// E on pattern(M_i).  Every list row has to store its diagonal block in A~.
 struct Fit8 {
     int nl = 0;                           // list rows
     const int32_t *list = nullptr, *abptr = nullptr, *abcol = nullptr;

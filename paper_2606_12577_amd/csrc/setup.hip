@@ -1800,6 +1800,13 @@ __global__ void k_pos_range(int B, const int32_t *__restrict__ where, int first,
     pos[i] = q >= 0 && q < n ? q : -1;
 }
 
+// miss[i] = 1 where block row i < n stores no diagonal block
+__global__ void k_no_diagonal(int n, const int32_t *__restrict__ ptr, const int32_t *__restrict__ col,
+                              int32_t *__restrict__ miss) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) miss[i] = bsearch_i32(col, ptr[i], ptr[i + 1], i) < 0 ? 1 : 0;
+}
+
 __global__ void k_iota(int32_t *a, int n) {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t < n) a[t] = t;
@@ -2934,6 +2941,18 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
     DBuf<int32_t> pos(B), cnt, err(B), redo, rec8;
     DBuf<uint16_t> pos8;
     const int maxdeg = max_span(c, B, 1, ap.ptr.get());
+    // The fused step finds E_i among the rows of a block's neighbours, so every
+    // smoothed row has to store its diagonal block.  Elliptic levels do (the
+    // prescaling needs a_kk > 0); a saddle-point level's block of pressures need
+    // not, and such a level takes the kernels that search for E_i's columns.
+    bool diagonals = true;
+    if (nb == 8 && L.kind.get() && B_act > 0) {
+        DBuf<int32_t> miss(B_act);
+        hipLaunchKernelGGL(k_no_diagonal, dim3(grid_for(B_act)), dim3(WG), 0, s, B_act, ap.ptr.get(), ap.col.get(),
+                           miss.get());
+        CS_LAUNCH_CHECK();
+        diagonals = reduce_i32(c, miss.get(), B_act, false) == 0;
+    }
     int32_t emax = 1, enext = 1;   // longest block row of E (E_0 = I), and of the updated one
     DBuf<int32_t> sing_all((size_t)depth * B);   // singular flags of all steps' rows, counted at the end
     int64_t nsing = 0;
@@ -3004,8 +3023,8 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
             };
             // every block in the list, in order: the new pattern is M's
             const bool all = o.mode == CS_ADDITIVE && !lattice && nl == B;
-            // 8x8 blocks whose rows of M fit in LDS: product, normal equations and
-            // update in one kernel, M never stored
+            // 8x8 blocks whose rows of M fit in LDS and hold E_i's columns: product,
+            // normal equations and update in one kernel, M never stored
             Fit8 f8;
             if (nb == 8) {
                 f8.nl = nl, f8.list = dlist;
@@ -3021,7 +3040,7 @@ void fit_level(Ctx &c, Level &L, const cs_options &o) {
                 hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(WG), 0, s, redo.get(), (int64_t)1, 0);
                 CS_LAUNCH_CHECK();
             }
-            const bool fused = nb == 8 && fit8_fits(f8);
+            const bool fused = nb == 8 && diagonals && fit8_fits(f8);
             DBuf<double> mval;
             if (fused) {
                 const size_t nrec = fit8_rec_ints(f8), npos = (size_t)nl * f8.pcap;

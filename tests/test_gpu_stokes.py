@@ -179,3 +179,82 @@ def test_overlapping_fp32_gmres(gpu_lib):
     x, ex = s.solve(p.rhs, rtol=1e-10, maxit=200, method="fgmres")
     assert ex["rel_res"] <= 1e-10
     print(f"mac64 Vanka exact: {ex['iterations']} it, rho {ex['rho']:.3f}")
+
+
+# ---------------------------------------------------------------------------
+# Blocks without a diagonal block
+# ---------------------------------------------------------------------------
+
+def pressure_blocks(dense):
+    """A two-level saddle-point hierarchy of 8x8 blocks: a chain of 12 velocity
+    blocks, then 6 blocks of pressures only, which store no diagonal block,
+    then `dense` coupled velocity blocks beside them (more than 64 neighbours
+    take the level to the general fit kernels)."""
+    import scipy.sparse as sp
+
+    from synth.problem import Level
+    rng = np.random.default_rng(11)
+    nb, bu, bp = 8, 12, 6
+    nu = nb * bu
+    V = np.kron(sp.diags([1.0, 1.0], [-1, 1], shape=(bu, bu)).toarray(), np.ones((nb, nb)))
+    V = V * rng.uniform(-1, 1, V.shape) / 32
+    V = V + V.T + 2.0 * np.eye(nu)
+    D = np.kron(np.kron(np.eye(bp), np.ones((1, 2))), np.ones((nb, nb))) * rng.uniform(-1, 1, (nb * bp, nu))
+    A = sp.bmat([[sp.csr_matrix(V), sp.csr_matrix(D.T)], [sp.csr_matrix(D), None]])
+    kind = np.r_[np.zeros(nu), np.ones(nb * bp)]
+    if dense:
+        m = nb * dense
+        A = sp.block_diag([A, rng.uniform(-1, 1, (m, m)) / m + np.eye(m)])
+        kind = np.r_[kind, np.zeros(m)]
+    A = sp.csr_matrix(A)
+    blocks = A.shape[0] // nb
+    levels = [Level(A, nb, sp.csr_matrix(sp.kron(sp.eye(blocks), np.ones((nb, 1)))), 1.0 / nb),
+              Level(sp.identity(blocks, format="csr"))]
+    levels[0].kind = kind.astype(np.int32)
+    levels[0].colour = np.r_[np.arange(bu) % 2, np.full(bp, 2), np.arange(dense)].astype(np.int32)
+    return levels, bu + bp
+
+
+def fit_on_stored_pattern(level, nblk, depth, groups):
+    """The cascade fit of the first nblk blocks with E kept on the block pattern
+    of A~ E, which drops the identity of a block that stores no diagonal block."""
+    nb = level.block_size
+    n = nb * nblk
+    A = level.A[:n, :n]
+    w, At = O.prescale(A, level.kind[:n], "l1")
+    At = At.toarray()
+    Apat = O.block_pattern(A, nb).toarray().astype(bool)
+    E, Epat = np.eye(n), np.eye(nblk, dtype=bool)
+    lam = [np.zeros((nblk, nb, nb)) for _ in range(depth)]
+    cond = [np.ones(nblk) for _ in range(depth)]
+    for ell in range(depth):
+        for blocks in groups:
+            M, Mpat = At @ E, (Apat.astype(int) @ Epat.astype(int)) > 0
+            Mb, Eb = M.reshape(nblk, nb, n)[blocks], E.reshape(nblk, nb, n)[blocks]
+            G, H = Mb @ Mb.transpose(0, 2, 1), Eb @ Mb.transpose(0, 2, 1)
+            Lt = O.least_squares_blocks(H, G)
+            lam[ell][blocks], cond[ell][blocks] = O.unscale(Lt, w.reshape(nblk, nb)[blocks].ravel()), O.gram_condition(G)
+            keep = np.repeat(Mpat[blocks], nb, axis=1)[:, None, :]
+            E.reshape(nblk, nb, n)[blocks] = (Eb - Lt @ Mb) * keep
+            Epat[blocks] = Mpat[blocks]
+    return dict(lam=lam, gram_cond=cond)
+
+
+@pytest.mark.parametrize("mode", ["additive", "multiplicative"])
+@pytest.mark.parametrize("dense", [0, 72])
+def test_blocks_of_pressures_only(gpu_lib, mode, dense):
+    levels, nblk = pressure_blocks(dense)
+    s = gpu_lib.Solver(levels)
+    s.setup(depth=3, mode=mode, order="FF")
+    if mode == "additive":
+        groups = [np.arange(nblk)]
+    else:
+        colour = levels[0].colour[:nblk]
+        groups = [np.flatnonzero(colour == k) for k in range(colour.max() + 1)]
+    ref = fit_on_stored_pattern(levels[0], nblk, 3, groups)
+    if mode == "additive":   # one step has no E to keep: the oracle's own fit
+        n = 8 * nblk
+        one = O.fit(levels[0].A[:n, :n], 8, 1, kind=levels[0].kind[:n], norm="l1")
+        np.testing.assert_allclose(ref["lam"][0], one["lam"][0], rtol=0, atol=1e-12)
+    check_level_smoothers(s, ref, 0, 3, f"pressure blocks {mode} dense={dense}", rows=np.arange(nblk))
+    s.close()
