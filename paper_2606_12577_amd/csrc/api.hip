@@ -521,6 +521,7 @@ cs_status cs_vcycle(cs_ctx ctx, const double *b, double *x, int32_t nrhs) {
     return guarded(ctx, [&](Ctx &c) {
         need(c.have_setup, "cs_vcycle before cs_setup", CS_ESTATE);
         need(b && x, "null vector");
+        need(nrhs == 1 || nrhs == 2 || nrhs == 4 || nrhs == 8, "nrhs must be 1, 2, 4 or 8");
         cs::vcycle_apply(c, b, x, nrhs);
         CS_HIP(hipStreamSynchronize(c.stream));
     });

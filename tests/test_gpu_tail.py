@@ -280,3 +280,17 @@ def test_tail_bf16_multicoloured(gpu_lib, blocks, grids, order, n_pre, n_post, d
             assert ib["iterations"] == ia["iterations"]
             np.testing.assert_array_equal(xb.cpu().numpy(), xa.cpu().numpy())
     s.close()
+
+
+@pytest.mark.parametrize("tail", [0, 4096])
+def test_right_hand_side_counts_with_a_tail(gpu_lib, tail):
+    """A V-cycle that is one tail launch refuses the counts that the per-level
+    launches refuse."""
+    p = fd.poisson2d(64)
+    s = gpu_lib.Solver(p.levels)
+    s.setup(depth=2)
+    s.set_tail(tail)
+    for nrhs in (3, 5, 16):
+        with pytest.raises(gpu_lib.CascadeError, match="nrhs must be 1, 2, 4 or 8"):
+            s.vcycle(np.ones((p.n, nrhs)))
+    s.close()
