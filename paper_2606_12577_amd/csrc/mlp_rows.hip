@@ -207,7 +207,12 @@ __global__ __launch_bounds__(RW) void k_rows(RowArgs a) {
         T3 = load_bt(a.W3, a.W, a.W, a.O);
         T2 = load_bt(a.W2, a.W, a.W, a.W);
     }
+    // The padded columns of a layer stay zero: an infinity in the row times a
+    // padded zero weight is a NaN there, which the next product would spread over
+    // the row.
     const bool inW = col < a.W, inO = col < a.O;
+    const uint32_t keep = inW ? ~0u : 0u;
+    auto pad = [&](float v) { return __uint_as_float(__float_as_uint(v) & keep); };
     const float b1 = inW ? a.b1[col] : 0.f, b2 = inW ? a.b2[col] : 0.f, b3 = inO ? a.b3[col] : 0.f;
     const float mean = inO ? a.mean[col] : 0.f, sd = inO ? a.std[col] : 1.f;
     float z1[RT][4], z2[RT][4], tt[RT][4];
@@ -229,7 +234,7 @@ __global__ __launch_bounds__(RW) void k_rows(RowArgs a) {
         for (int u = 0; u < 4; ++u) each([&](int i, int r, int row, int gm) { z1[i][r] += pv[u][i][r]; });
     }
     each([&](int i, int r, int row, int gm) {
-        const float v = z1[i][r] + b1, h = v * sigmoid(v);
+        const float v = z1[i][r] + b1, h = pad(v * sigmoid(v));
         z1[i][r] = v;
         At[row][col] = h;
         if constexpr (MODE == ROWS_TRAIN)
@@ -239,7 +244,7 @@ __global__ __launch_bounds__(RW) void k_rows(RowArgs a) {
     product(B2);
     __syncthreads();
     each([&](int i, int r, int row, int gm) {
-        const float v = acc[i][r] + b2, h = v * sigmoid(v);
+        const float v = acc[i][r] + b2, h = pad(v * sigmoid(v));
         z2[i][r] = v;
         At[row][col] = h;
         if constexpr (MODE == ROWS_TRAIN)
@@ -287,7 +292,7 @@ __global__ __launch_bounds__(RW) void k_rows(RowArgs a) {
         product(T3);   // dy W3
         __syncthreads();
         each([&](int i, int r, int row, int gm) {
-            const float d = acc[i][r] * dsilu(z2[i][r]);
+            const float d = pad(acc[i][r] * dsilu(z2[i][r]));
             acc[i][r] = d;
             At[row][col] = d;
             if (gm < a.M) a.d2[(int64_t)gm * NP + col] = d;

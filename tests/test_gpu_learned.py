@@ -217,3 +217,25 @@ def test_setup_learned_validation(gpu_lib, L):
         net.set_scaling(np.zeros(2), np.array([1.0, 0.0]))      # std must be positive
     with pytest.raises(cascade.CascadeError):
         net.set_params(np.full(net.n_params, np.nan))
+
+
+@pytest.mark.parametrize("n", [40, 16400])   # 16- and 64-row tiles
+@pytest.mark.parametrize("width,n_out", [(20, 16), (64, 40), (128, 128)])
+def test_rows_that_overflow_stay_infinite(gpu_lib, L, width, n_out, n):
+    """Positive weights: a row with an infinite or overflowing input predicts
+    +inf (no NaN from the columns that pad a layer to 128), the others as usual."""
+    import torch
+    n_in = 24
+    net = L.Mlp(n_in, width, n_out)
+    net.set_params(np.full(net.n_params, 0.125, np.float32))
+    net.set_scaling(np.zeros(n_out), np.ones(n_out))
+    X = torch.full((n, n_in), 0.5)
+    X[3, 5] = float("inf")
+    X[n - 1] = 3e38
+    h = X
+    for k, fan_in in enumerate((n_in, width, width)):
+        z = h @ torch.full((fan_in, width if k < 2 else n_out), 0.125) + 0.125
+        h = z * torch.sigmoid(z) if k < 2 else z
+    y = net.forward(X).cpu().numpy()
+    assert np.isposinf(h[[3, n - 1]].numpy()).all()
+    np.testing.assert_allclose(y, h.numpy(), rtol=1e-5)
