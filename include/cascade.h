@@ -358,7 +358,8 @@ cs_status cs_get_graphs(cs_ctx ctx, int32_t *on, double *eager_ms, double *graph
  * V-cycle with the tail off and starting at each level of at most 65536 rows
  * and keeps the fastest.  cs_vcycle_noalloc always runs the per-level launches.
  * cs_get_tail returns max_rows, the first level the tail covers in the current
- * setup (-1: none) and, when cap > 0, up to cap of the last autotune's
+ * setup for as many right-hand sides as the last V-cycle, solve or autotune had
+ * (one before the first; -1: none) and, when cap > 0, up to cap of the last autotune's
  * candidates (cand_rows: the limit, 0 = off; cand_ms: one V-cycle in ms) with
  * their count in *n_cand (may be null).  Errors: CS_EINVAL for max_rows < 0 or
  * max_rows > 65536. */

@@ -745,7 +745,7 @@ cs_status cs_get_tail(cs_ctx ctx, int64_t *max_rows, int32_t *first_level, int32
         need(max_rows != nullptr && first_level != nullptr, "null output");
         need(cap >= 0 && (cap == 0 || (cand_rows != nullptr && cand_ms != nullptr)), "candidate arrays");
         *max_rows = c.tail_rows;
-        *first_level = c.have_setup ? cs::tail_start(c) : -1;
+        *first_level = c.have_setup ? cs::tail_start(c, c.ws_nrhs > 0 ? c.ws_nrhs : 1) : -1;
         const int nt = (int)c.tune_tail_rows.size();
         for (int k = 0; k < std::min(nt, (int)cap); ++k) {
             cand_rows[k] = c.tune_tail_rows[k];

@@ -393,7 +393,7 @@ void autotune(Ctx &c, int nrhs, double *ms_out);
 void tune_graphs(Ctx &c, int nrhs, double *eager_ms, double *graph_ms);
 
 // tail.hip: the small levels in one launch
-int tail_start(const Ctx &c, int nrhs = 1);
+int tail_start(const Ctx &c, int nrhs);
 void tail_prepare(Ctx &c, int nrhs);
 // whether the tail runs the V-cycle from level l for nrhs right-hand sides
 inline bool tail_covers(const Ctx &c, int l, int nrhs) {

@@ -294,3 +294,22 @@ def test_right_hand_side_counts_with_a_tail(gpu_lib, tail):
         with pytest.raises(gpu_lib.CascadeError, match="nrhs must be 1, 2, 4 or 8"):
             s.vcycle(np.ones((p.n, nrhs)))
     s.close()
+
+
+def test_tail_level_is_reported_for_the_right_hand_sides_in_use(gpu_lib):
+    """The BF16 multicoloured tail takes one right-hand side: with two the
+    V-cycle runs per-level launches, and cs_get_tail says so."""
+    from synth import dg
+    levels = dg.sipg_q3(12).levels
+    s = gpu_lib.Solver(levels)
+    s.setup(depth=2, mode="multiplicative", order="FF", ridge=1e-3, precision="bf16")
+    s.set_tail(levels[0].n)
+    b = np.random.default_rng(3).uniform(-1, 1, size=(levels[0].n, 2))
+    assert s.tail() == (levels[0].n, 0)      # no V-cycle yet: one
+    for nrhs, first in ((2, -1), (1, 0)):
+        s.trace(("tail",))
+        s.vcycle(b[:, :nrhs])
+        s.trace(())
+        assert s.tail() == (levels[0].n, first)
+        assert (s.trace_read()["tail"]["launches"] > 0) == (first == 0)
+    s.close()
