@@ -28,6 +28,13 @@ struct Error {
 
 #define CS_LAUNCH_CHECK() CS_HIP(hipGetLastError())
 
+// Dynamic LDS beyond 64 KB has to be allowed per kernel.  The limit is the
+// process's, not a context's or a launch's: every caller gives the same one, the
+// most that the kernel may ever use, so that none lowers it under another.
+inline void allow_lds(const void *kernel, int64_t bytes) {
+    CS_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+}
+
 // Map the hardware workgroup id (of G) to a logical index so that each of the
 // 8 XCDs (which receive workgroups round-robin) works through one contiguous
 // range: neighbouring rows, which read the same gathered data, then run on the
@@ -404,7 +411,7 @@ int tail16_rounds(const Level &L);
 int64_t tail16_schedule_words(const Level &L);
 void tail16_schedule(const Level &L, uint32_t zero, std::vector<int32_t> &out);
 int64_t tail16_pack(Ctx &c, const Level &L, unsigned short *out);
-void tail16_prepare(Ctx &c);
+void tail16_prepare(int64_t lds);
 void tail16_launch(Ctx &c, hipEvent_t ev0, hipEvent_t ev1, const double *b64, double *x64, bool add);
 
 // solve.hip

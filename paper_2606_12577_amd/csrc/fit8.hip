@@ -391,9 +391,7 @@ __global__ __launch_bounds__(WGS, REDO ? 2 : 4) void k_fit8(const int32_t *__res
 template <int WGS, bool REDO>
 void go(hipStream_t s, const Fit8 &f) {
     const int64_t bytes = fit8_bytes(f, WGS / 64);
-    if (bytes > 65536)
-        CS_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_fit8<WGS, REDO>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+    allow_lds(reinterpret_cast<const void *>(&k_fit8<WGS, REDO>), FIT8_LDS);
     const unsigned grid = REDO ? 256u : (unsigned)f.nl;
     // rows in flight on an XCD (32 CUs): LDS, five wavefronts per SIMD
     const int ahead = 32 * (int)std::max<int64_t>(std::min<int64_t>(2 * FIT8_LDS / bytes, 20 * 64 / WGS), 1);

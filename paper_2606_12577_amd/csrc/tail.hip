@@ -564,12 +564,10 @@ void tail_table(Ctx &c, int nrhs) {
     c.tail_bytes = bytes;
     c.tail_tab.upload(c.tail_host.data(), c.tail_host.size(), c.stream);
     c.tail_sys.upload(c.tail_sys_host.data(), c.tail_sys_host.size(), c.stream);
-    if (c.tail_b16) tail16_prepare(c);
+    if (c.tail_b16) tail16_prepare(tail_lds_limit(c));
     else tail_dispatch((int)c.lv[from].nb, [&](auto nbc) {
         constexpr int NB = decltype(nbc)::value;
-        CS_HIP(   // more than 64 KB of dynamic LDS has to be asked for
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_tail_vcycle<T, NB>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.tail_lds));
+        allow_lds(reinterpret_cast<const void *>(&k_tail_vcycle<T, NB>), tail_lds_limit(c));
     });
     c.tail_gen = c.gen;
     c.tail_prec = c.precision;

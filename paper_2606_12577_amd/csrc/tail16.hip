@@ -337,11 +337,7 @@ int64_t tail16_pack(Ctx &c, const Level &L, unsigned short *out) {
     return rows * ROW16;
 }
 
-// More than 64 KB of dynamic LDS has to be asked for.
-void tail16_prepare(Ctx &c) {
-    CS_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_tail_bsr16),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.tail_lds));
-}
+void tail16_prepare(int64_t lds) { allow_lds(reinterpret_cast<const void *>(&k_tail_bsr16), lds); }
 
 void tail16_launch(Ctx &c, hipEvent_t ev0, hipEvent_t ev1, const double *b64, double *x64, bool add) {
     hipExtLaunchKernelGGL(k_tail_bsr16, dim3(8 * (1 + TAIL_HELPERS)), dim3(TAIL_WG), (unsigned)c.tail_lds, c.stream, ev0, ev1, 0,

@@ -313,3 +313,28 @@ def test_tail_level_is_reported_for_the_right_hand_sides_in_use(gpu_lib):
         assert s.tail() == (levels[0].n, first)
         assert (s.trace_read()["tail"]["launches"] > 0) == (first == 0)
     s.close()
+
+
+@pytest.mark.parametrize("family", ["points", "bf16"])
+def test_tail_of_one_solver_beside_a_smaller_one(gpu_lib, family):
+    """Two live solvers whose tails run the same kernel: the second one's, with
+    less LDS, does not take the first one's away."""
+    def make(n):
+        if family == "points":
+            p = fd.poisson2d(n)
+            return p.levels, p.rhs, dict(depth=2)
+        from synth import dg
+        p = dg.sipg_q3(n)
+        return p.levels, p.rhs, dict(depth=2, mode="multiplicative", order="FF", ridge=1e-3, precision="bf16")
+    solvers = []
+    for n in ((64, 16) if family == "points" else (12, 8)):
+        levels, b, opts = make(n)
+        s = gpu_lib.Solver(levels)
+        s.setup(**opts)
+        x0 = _vcycle(s, b[:, :1], 0)
+        np.testing.assert_array_equal(_vcycle(s, b[:, :1], levels[0].n), x0)
+        assert s.tail()[1] == 0
+        solvers.append((s, b[:, :1], x0))
+    for s, b, x0 in solvers:
+        np.testing.assert_array_equal(s.vcycle(b).cpu().numpy(), x0)
+        s.close()
