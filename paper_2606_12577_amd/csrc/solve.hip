@@ -980,6 +980,13 @@ __global__ __launch_bounds__(WG) void k_cg_zq_flat(int64_t npairs, int nsys, con
 // k_reduce_partials (N = 1024 accumulators) or k_wg_to_sys (256): the same bits,
 // without a launch of 3 to 4 us between the kernel that leaves the partials and
 // the one that uses them.  The sums in red[0, W), after a barrier.
+// Every workgroup adds all of them, so this takes G^2 R loads: it pays up to
+// G R = FOLD_PARTIALS, workgroups (of the largest system) times right-hand sides.
+// CG iteration in us, summed by a launch of its own and folded, FP32 V-cycle: 64^2
+// 63.2 / 59.6, 512^2 (G = 1024) with 1, 2, 4 and 8 right-hand sides 135.2 / 119.0,
+// 136.4 / 131.7, 155.7 / 156.8 and 195.2 / 205.7; 64^3 114.7 / 108.6, 117.4 / 117.3,
+// 136.9 / 142.7 and 181.0 / 195.2; 128^3 with 8 828 / 848.
+constexpr int64_t FOLD_PARTIALS = 2048;
 template <int N, int W>
 __device__ __forceinline__ void fold_partials(const double *__restrict__ partial, int64_t n, double *red) {
 #pragma unroll
@@ -997,22 +1004,23 @@ __device__ __forceinline__ void fold_partials(const double *__restrict__ partial
 }
 
 // p = z + beta p (first: p = z), beta = -(z, q_prev) / (p_prev, q_prev), (z, q_prev)
-// from the partials of k_cg_zq_flat
+// from the partials of k_cg_zq_flat (fold) or their sums [nsys][R]
 template <typename T, int R>
 __global__ __launch_bounds__(WG) void k_cg_p_flat(int64_t npairs, int nsys, const int32_t *__restrict__ sys_wg,
                                                   const int64_t *__restrict__ sys_ptr, const T *__restrict__ z,
-                                                  const double *__restrict__ zq_part,
+                                                  const double *__restrict__ zq_in, int fold,
                                                   const double *__restrict__ pq_prev, double *__restrict__ p,
                                                   int first) {
-    __shared__ double zq[1024];
+    __shared__ double red[1024];
     const PairRange pr = pair_range<R>(npairs, nsys, sys_wg, sys_ptr);
     double beta[2] = {0.0, 0.0};
     if (!first) {
-        if (sys_wg)
-            fold_partials<256, R>(zq_part + (int64_t)sys_wg[pr.sys] * R,
-                                  (int64_t)(sys_wg[pr.sys + 1] - sys_wg[pr.sys]) * R, zq);
-        else
-            fold_partials<1024, R>(zq_part, (int64_t)gridDim.x * R, zq);
+        const double *zq = fold ? red : zq_in + pr.sys * R;
+        if (fold && sys_wg)
+            fold_partials<256, R>(zq_in + (int64_t)sys_wg[pr.sys] * R,
+                                  (int64_t)(sys_wg[pr.sys + 1] - sys_wg[pr.sys]) * R, red);
+        else if (fold)
+            fold_partials<1024, R>(zq_in, (int64_t)gridDim.x * R, red);
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int k = (int)((2 * pr.begin + u) % R);
@@ -1032,9 +1040,9 @@ __global__ __launch_bounds__(WG) void k_cg_p_flat(int64_t npairs, int nsys, cons
     }
 }
 
-// x += alpha p, r -= alpha q, rt = r (working precision), partial r^2.  One
-// system: (p, q) and (p, r) from the n_part partials of k_cg_ap, kept in pq
-// for the next direction; a batch: from pq.
+// x += alpha p, r -= alpha q, rt = r (working precision), partial r^2.  (p, q)
+// and (p, r) from the n_part partials of k_cg_ap, kept in pq for the next
+// direction (one system), or from pq (n_part 0).
 template <typename T, int R>
 __global__ __launch_bounds__(WG) void k_cg_update_flat(int64_t npairs, int nsys, const int32_t *__restrict__ sys_wg,
                                                        const int64_t *__restrict__ sys_ptr,
@@ -1046,16 +1054,16 @@ __global__ __launch_bounds__(WG) void k_cg_update_flat(int64_t npairs, int nsys,
     __shared__ double red[1024];
     const PairRange pr = pair_range<R>(npairs, nsys, sys_wg, sys_ptr);
     double alpha[2];
-    const double *dots = pq + pr.sys * 2 * R;
-    if (!sys_wg) {
+    const double *dots = n_part ? red : pq + pr.sys * 2 * R;
+    if (n_part) {
         fold_partials<1024, 2 * R>(pq_part, n_part * 2 * R, red);
         if (blockIdx.x == 0 && threadIdx.x < 2 * R) pq[threadIdx.x] = red[threadIdx.x];
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int k = (int)((2 * pr.begin + u) % R);
-        const double d = sys_wg ? dots[k] : red[k], n = sys_wg ? dots[R + k] : red[R + k];
-        alpha[u] = d > 0.0 ? n / d : 0.0;
+        const double d = dots[k];
+        alpha[u] = d > 0.0 ? dots[R + k] / d : 0.0;
         if (!isfinite(alpha[u])) alpha[u] = 0.0;
     }
     double v[2] = {0.0, 0.0};
@@ -2587,7 +2595,7 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
             // flat pair streaming: one system of even length, or a batch with R even
             // (pairs then never straddle two systems)
             const bool flat = batch ? R % 2 == 0 : (L0.n * R) % 2 == 0;
-            int64_t Gf = G;                      // workgroups of the flat kernels
+            int64_t Gf = G, fold_wgs = G;        // workgroups of the flat kernels, most of a system
             const int32_t *sys_wg = nullptr;
             if (batch && flat) {
                 std::vector<int32_t> wg(nsys + 1, 0);
@@ -2595,6 +2603,8 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                     wg[q2 + 1] = wg[q2] + (int32_t)ceil_div((c.sys_ptr[q2 + 1] - c.sys_ptr[q2]) * R / 2, SYS_CHUNK);
                 c.cg_sys_wg.upload(wg.data(), wg.size(), c.stream);
                 Gf = wg[nsys];
+                fold_wgs = 0;
+                for (int q2 = 0; q2 < nsys; ++q2) fold_wgs = std::max<int64_t>(fold_wgs, wg[q2 + 1] - wg[q2]);
                 sys_wg = c.cg_sys_wg.get();
                 if (c.cg_partial.n < (size_t)(Gf * R)) c.cg_partial.alloc(Gf * R);
             }
@@ -2607,6 +2617,8 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                     hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(1024), 0, c.stream, Gf, R, fpart, out, host);
                 CS_LAUNCH_CHECK();
             };
+            const bool fold_zq = flat && fold_wgs * R <= FOLD_PARTIALS;
+            const bool fold_pq = flat && !batch && G * R <= FOLD_PARTIALS;
             // ||b||^2 and rt = b; r = b; x = 0
             if (batch)
                 hipLaunchKernelGGL((k_ir_residual<T, R, true>), dim3(G), dim3(WG), 0, c.stream, S.nrows, S.nslices,
@@ -2639,6 +2651,7 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                         hipLaunchKernelGGL((k_cg_zq_flat<T, R>), dim3(Gf), dim3(WG), 0, c.stream, npairs, nsys, sys_wg,
                                            c.sys_ptr_d.get(), z, q, fpart);
                         CS_LAUNCH_CHECK();
+                        if (!fold_zq) reduce_flat(c.cg_zq.get(), nullptr);
                     } else {
                         if (batch)
                             hipLaunchKernelGGL((k_cg_zq<T, R, true>), dim3(G), dim3(WG), 0, c.stream, S.nrows,
@@ -2657,7 +2670,8 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                                        c.sys_ptr_d.get(), z, c.cg_zq.get(), pq, p, first ? 1 : 0);
                 else
                     hipLaunchKernelGGL((k_cg_p_flat<T, R>), dim3(Gf), dim3(WG), 0, c.stream, npairs, nsys, sys_wg,
-                                       c.sys_ptr_d.get(), z, fpart, pq, p, first ? 1 : 0);
+                                       c.sys_ptr_d.get(), z, fold_zq ? fpart : c.cg_zq.get(), fold_zq ? 1 : 0, pq, p,
+                                       first ? 1 : 0);
                 CS_LAUNCH_CHECK();
                 trace_end(c, slot);
                 slot = trace_begin(c, CS_TRACE_REFINE, S.nnz * 12.0 + 3.0 * vec);
@@ -2677,12 +2691,13 @@ void solve_cg(Ctx &c, const double *b, double *x, int nrhs, double rtol, int max
                                            c.ir_partial.get());
                     });
                 CS_LAUNCH_CHECK();
-                if (batch || !flat) reduce(2 * R, pq);
+                if (!fold_pq) reduce(2 * R, pq);
                 trace_end(c, slot);
                 slot = trace_begin(c, CS_TRACE_REFINE, 6.0 * vec + L0.n * R * sizeof(T));
                 if (flat) {
                     hipLaunchKernelGGL((k_cg_update_flat<T, R>), dim3(Gf), dim3(WG), 0, c.stream, npairs, nsys, sys_wg,
-                                       c.sys_ptr_d.get(), pq, c.ir_partial.get(), G, p, q, x, r, rt, fpart);
+                                       c.sys_ptr_d.get(), pq, c.ir_partial.get(), fold_pq ? G : 0, p, q, x, r, rt,
+                                       fpart);
                     CS_LAUNCH_CHECK();
                     reduce_flat(c.ir_norm.get(), c.h_norm);
                 } else {

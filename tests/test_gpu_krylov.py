@@ -251,3 +251,25 @@ def test_cg_sizes_and_first_solve(gpu_lib, n, nrhs):
         x2, i2 = s.solve(p.rhs, **kw)
         np.testing.assert_array_equal(x2.cpu().numpy(), x.cpu().numpy())
         np.testing.assert_array_equal(i2["history"], info["history"])
+
+
+@pytest.mark.parametrize("sizes", [(256,), (272,), (256, 16), (272, 16)])
+def test_cg_sums_folded_and_in_their_own_launch(gpu_lib, sizes):
+    """Eight right-hand sides: up to 256 workgroups (65,536 rows) the kernels fold
+    the dot products' partials themselves, from 257 on a launch adds them."""
+    probs = [fd.poisson2d(n, nrhs=8) for n in sizes]
+    sms = [O.setup_hierarchy(p.levels, 1) for p in probs]
+    bt = concatenate(probs)
+    s = gpu_lib.Solver(bt.levels)
+    s.setup(depth=1)
+    if len(sizes) > 1:
+        s.set_systems(bt.sys_ptr)
+    x, info = s.solve(bt.rhs, rtol=1e-30, maxit=4, method="cg", raise_on_noconv=False)
+    xs = bt.split(x.cpu().numpy())
+    for k, si in enumerate(bt.order):
+        p = probs[si]
+        xo, ho = O.fcg(p.levels[0].A, lambda v: O.vcycle(p.levels, sms[si], v), p.rhs, rtol=1e-30, maxit=4)
+        check_vec(xs[si], xo, 1e-8, f"FCG iterate, poisson {sizes[si]}")
+        if len(sizes) == 1:
+            np.testing.assert_allclose(info["history"], ho, rtol=1e-6)
+    s.close()
