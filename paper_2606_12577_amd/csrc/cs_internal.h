@@ -192,6 +192,7 @@ struct Level {
     int64_t n_active = 0;
     int64_t act_slices = 0;           // SELL slices covering the active rows
     int64_t act_nnz = 0;              // entries of A in the active rows
+    int act_row = 0;                  // entries of the longest of them
     std::vector<int64_t> dseg;        // absolute row offsets, size ndseg + 1
     DBuf<int64_t> dseg_d, dinv_off;   // device copies: offsets and inverse offsets
     DBuf<double> dinv;                // concatenated row-major inverses

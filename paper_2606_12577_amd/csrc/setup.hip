@@ -2589,6 +2589,8 @@ void build_level_device(Ctx &c, Level &L) {
     build_sell(L.sell, L.h_ptr, L.h_col, L.h_val, nullptr, s);
     L.act_slices = ceil_div(L.n_active, 64);
     L.act_nnz = L.h_ptr[L.n_active];
+    L.act_row = 0;
+    for (int64_t r = 0; r < L.n_active; ++r) L.act_row = std::max(L.act_row, (int)(L.h_ptr[r + 1] - L.h_ptr[r]));
     // direct segments: offsets of their dense inverses in dinv
     const int nseg = (int)L.dseg.size() - 1;
     if (nseg > 0) {

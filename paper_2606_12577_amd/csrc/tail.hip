@@ -416,10 +416,28 @@ static int64_t tail16_extra(const Ctx &c, bool b16, int from) {
     return b16 ? n + 64 : 0;
 }
 
+// A level of general transfers whose rows are too long for registers streams A
+// from the L2 through one CU in every sweep, 12 us for 39,300 entries in FP64 and
+// 9 in FP32, which a launch per step does on all of them: such a level is covered
+// up to STREAM_MAX bytes of A, or STREAM_MAX0 where the tail is the whole V-cycle
+// (its A stays in the L2, and no conversions are launched).  One V-cycle of the
+// 27-point problem, per-level launches / tail, one right-hand side: 24^3 from 1,728
+// rows in FP32 (307 KB) 101 / 90 us and in FP64 (460 KB) 103 / 108, 48^3 from there
+// 125 / 128 and 132 / 163; 32^3 from 4,096 rows (760 KB, 1,140 KB) 125 / 129 and
+// 126 / 184; from level 0 12^3 in FP64 (460 KB) 76 / 71, 16^3 in FP32 (760 KB)
+// 102 / 87 and in FP64 (1,140 KB) 102 / 135.
+constexpr int64_t STREAM_MAX = 320 << 10, STREAM_MAX0 = 800 << 10;
+
+static bool tail_streams_well(const Ctx &c, int l) {
+    const Level &L = c.lv[l];
+    if ((c.fuse_transfers && L.agg_k > 0) || L.act_row <= (L.nb == 1 ? tail_ml<1>() : tail_ml<8>())) return true;
+    return L.act_nnz * (c.precision == CS_FP64 ? 12 : 8) <= (l == 0 ? STREAM_MAX0 : STREAM_MAX);
+}
+
 // The levels the tail kernel covers: the first level l (the finest included)
 // from which every level has at most c.tail_rows rows, every smoothed one is
 // additive (no overlapping blocks) with one common block size of 1, 2, 4 or 8,
-// the cycle pre- and post-smooths, and a system's vectors on all covered levels
+// none streams more than it may, the cycle pre- and post-smooths, and a system's vectors on all covered levels
 // fit a workgroup's LDS; -1 when there is none.  Multicoloured levels are
 // covered where the sweeps run in BF16 (16x16 blocks, one right-hand side, no
 // direct segments above the last level).
@@ -436,6 +454,8 @@ int tail_start(const Ctx &c, int nrhs) {
         if (l + 1 < nl) ok = ok && V.depth >= 1 && V.nb == nb && V.n_active > 0;
         if (l + 1 < nl && b16)
             ok = ok && use_bf16(c, V) && !V.h_bmeta.empty() && V.lam16.get() && V.n_active == V.n;
+        else if (l + 1 < nl)
+            ok = ok && tail_streams_well(c, l);
         if (!ok) break;
         from = l;
     }
@@ -494,8 +514,7 @@ void tail_table(Ctx &c, int nrhs) {
             bytes += A + 2.0 * v + 2.0 * (double)L.nc * vr + (agg ? 0.0 : 2.0 * L.p_nnz * (es + 4.0));   // transfers
             t.lam = pick<T>(L.lam64, L.lam32);
             t.lamT = pick<T>(L.lam64T, L.lam32T);
-            for (int64_t r = 0; r < L.n_active; ++r)
-                t.max_len = std::max(t.max_len, (int)(L.h_ptr[r + 1] - L.h_ptr[r]));
+            t.max_len = L.act_row;
             if (c.tail_b16) {
                 t.nitems = tail16_rounds(L);
                 t.sched = (int)(soff / 4);

@@ -338,3 +338,27 @@ def test_tail_of_one_solver_beside_a_smaller_one(gpu_lib, family):
     for s, b, x0 in solvers:
         np.testing.assert_array_equal(s.vcycle(b).cpu().numpy(), x0)
         s.close()
+
+
+@pytest.mark.parametrize("n,precision,first", [
+    (12, "fp64", 0),     # 460 KB of A at level 0
+    (16, "fp32", 0),     # 760 KB
+    (16, "fp64", 1),     # 1,140 KB: from 512 rows
+    (24, "fp32", 1),     # 307 KB at level 1
+    (24, "fp64", -1),    # 460 KB there, and nothing below it to smooth
+    (32, "fp32", 2),     # 760 KB at level 1: from 512 rows
+])
+def test_tail_covers_streamed_levels_up_to_a_size(gpu_lib, n, precision, first):
+    """Long rows under general transfers: covered while one CU keeps up with a
+    launch per step, whatever larger limit is set."""
+    from synth import fe
+    levels = fe.multiphase3d(n).levels
+    b = np.random.default_rng(n).standard_normal((levels[0].n, 2))
+    s = gpu_lib.Solver(levels)
+    s.setup(depth=2, precision=precision)
+    s.set_tail(4096)
+    assert s.tail() == (4096, first)
+    x1 = s.vcycle(b).cpu().numpy()
+    s.set_tail(0)
+    np.testing.assert_array_equal(s.vcycle(b).cpu().numpy(), x1)
+    s.close()
