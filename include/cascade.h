@@ -341,19 +341,20 @@ cs_status cs_get_graphs(cs_ctx ctx, int32_t *on, double *eager_ms, double *graph
  * cost a kernel launch per sweep, transfer and direct solve while moving almost
  * no data; from the first level (the finest included) at which every level has
  * at most max_rows rows and the vectors of one system and right-hand side on
- * all remaining levels fit the LDS of a CU (about 5,900 rows in FP64, 11,900 in
- * FP32, the finest of them), the V-cycle from there down is one launch, a
- * workgroup per system and right-hand side, that runs the same per-row
- * arithmetic with workgroup barriers in place of kernel boundaries, so results
+ * all remaining levels fit the LDS of a CU (twice the rows of all levels and once
+ * those of the largest in 160 KB: about 5,580 rows in FP64 and 11,170 in FP32 for the
+ * finest where levels shrink by 4, 6,230 and 12,460 by 8; long rows under general
+ * transfers: up to 320 KB of A per level, 800 KB at level 0), the V-cycle from there
+ * down is one launch, a workgroup per system and right-hand side, that runs the same
+ * per-row arithmetic with workgroup barriers in place of kernel boundaries, so results
  * are bit-identical to the per-level launches.  It applies to additive cascades
  * with one block size of 1, 2, 4 or 8 on the covered levels and, with one
  * right-hand side and no independent systems, to multicoloured ones in CS_BF16
  * (blocks of 16; the schedule of a level takes LDS too, which leaves about 3,000
  * rows), n_pre >= 1 and n_post >= 1; other hierarchies run the per-level
- * launches.  The systems are
- * those of cs_set_systems where the transfers are aggregations and no row of a
- * covered level couples two of them, else there is one.  max_rows 0 switches it
- * off (the default).  One workgroup walks a system's rows 1024 at a time, so
+ * launches.  The systems are those of cs_set_systems where the transfers are
+ * aggregations and no row of a covered level couples two of them, else there is
+ * one.  max_rows 0 switches it off (the default).  One workgroup walks a system's rows 1024 at a time, so
  * the tail pays only on levels of a few thousand rows; cs_autotune times one
  * V-cycle with the tail off and starting at each level of at most 65536 rows
  * and keeps the fastest.  cs_vcycle_noalloc always runs the per-level launches.

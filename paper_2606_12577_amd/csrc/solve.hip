@@ -1468,10 +1468,14 @@ inline unsigned tile_grid(const Ctx &c, int64_t nslices) {
 
 // Workgroup size of a SELL kernel whose workgroups are independent slices: one
 // slice per workgroup up to four per CU, so that four wavefronts do not queue for
-// one CU's vector cache while other CUs are idle.  48^3 multi-phase problem, FP64,
-// two right-hand sides: residual of 13,824 and 1,728 rows (27 entries) 6.2 and
-// 5.7 us with four slices per workgroup, 5.4 and 4.2 with one; restriction from
-// them and from 110,592 rows (64 entries) 7.4, 5.8 and 7.5, now 5.7, 4.9 and 6.0.
+// one CU's vector cache while other CUs are idle.  us with four slices per workgroup
+// and with one, levels in descending size: 48^3 multi-phase problem (27 entries),
+// residual of 13,824 and 1,728 rows in FP64 with two right-hand sides 5.1 / 4.1 and
+// 5.0 / 3.8, with eight 14.9 / 9.4 and 13.9 / 7.8, in FP32 with one 5.1 / 3.9 and
+// 4.8 / 3.6; restriction from 110,592 rows 7.8 / 5.9, 20.3 / 10.9 and 5.3 / 4.6.  32^2
+// SIPG (16 x 16 blocks), residual of 16,384 rows in FP64 11.2 / 8.8, restriction 9.1 /
+// 7.0.  64^2 Stokes, FP64, residual of 4,096 rows 4.2 / 3.6.  Interpolation 3.8 / 3.4
+// at 13,824 rows, but 2.4 / 2.8 at 256 to 1,024.
 inline int slice_wgs(int64_t nslices) { return nslices <= 1024 ? 64 : WG; }
 inline unsigned slice_grid(const Ctx &c, int64_t nslices) {
     return slice_wgs(nslices) == 64 ? (unsigned)nslices : tile_grid(c, nslices);
@@ -1523,9 +1527,11 @@ const float *pval<float>(const Level &L, bool tr) { return tr ? L.pt_val32.get()
 
 // Sweeps that take spmv_row_deep: rows longer than one chunk of eight on average
 // (8x8 blocks, up to two right-hand sides: what the registers hold), and no more
-// slices than the chip has SIMDs.  FP64, 27 entries per row, two right-hand sides:
-// 13,824 rows 6.0 -> 4.8 us, 1,728 rows 5.3 -> 4.9; 110,592 rows (1,728 slices)
-// 11.0 in chunks, 11.3 whole.  Residual and transfers gained nothing from it.
+// slices than the chip has SIMDs.  27 entries per row, us in chunks and whole, 13,824
+// and 1,728 rows: FP64 with one right-hand side 5.4 / 3.8 and 5.2 / 3.8, with two 6.5 /
+// 5.2 and 6.0 / 5.0, FP32 with one 4.2 / 4.0 and 4.0 / 3.9, with two 4.4 / 3.9 and 4.4 /
+// 3.8; 110,592 rows (1,728 slices) in FP64 11.0 / 11.3.  Residual and transfers gained
+// nothing from it.
 inline bool deep_rows(int64_t nslices, int64_t nrows, int64_t nnz) { return nslices <= DEEP_SLICES && nnz > 8 * nrows; }
 
 // Algorithmic bytes of one sweep launch: A's entries with their column index
